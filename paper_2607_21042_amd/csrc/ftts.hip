@@ -153,6 +153,7 @@ struct PrefillWs {
     int32_t* active; // [B] all ones (head GEMV reads no flags; kept for symmetry)
     float* part;     // split-K partial tiles of the GEMMs (16-bit modes, short prefixes)
     uint32_t* count; // their per-tile arrival counters
+    int32_t* slots;  // [M] KV slot of every row
 };
 
 // The persistent decode step's control words and exchange buffers sit at the
@@ -266,7 +267,10 @@ size_t prefill_bytes(const ftts_config& c, int B, int M, PrefillWs* out, char* b
     gemm_scratch(c, M, &pf, &cn);
     char* part = pf ? take(pf * 4) : nullptr;
     char* count = cn ? take(cn * 4) : nullptr;
-    if (out) *out = PrefillWs{(float*)x, a, qkv, h, (float*)xl, (int32_t*)act, (float*)part, (uint32_t*)count};
+    char* slots = take((size_t)M * 4);
+    if (out)
+        *out = PrefillWs{(float*)x,   a,     qkv, h, (float*)xl, (int32_t*)act, (float*)part, (uint32_t*)count,
+                         (int32_t*)slots};
     return off;
 }
 
@@ -727,11 +731,11 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
         as.x = P.x;
         if ((e = launch_assemble_prefix(c.wdtype, as, Mi, st)) != hipSuccess) return hip_fail(e, "input assembly");
     }
-    if (P.count) {
-        size_t pf, cn;
-        gemm_scratch(c, Mi, &pf, &cn);
-        if ((e = launch_fill_u32(P.count, cn, 0u, st)) != hipSuccess) return hip_fail(e, "gemm counters");
-    }
+    size_t pf = 0, cn = 0;
+    if (P.count) gemm_scratch(c, Mi, &pf, &cn);
+    if ((e = launch_prefill_setup(seqs, pt->block_table, pt->max_pages, kv->n_pages, Mi, P.slots, P.count, cn, st)) !=
+        hipSuccess)
+        return hip_fail(e, "prefill setup");
 
     KvAppend kva{};
     kva.base = kv->base;
@@ -740,6 +744,7 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
     kva.d_model = d;
     kva.max_pages = pt->max_pages;
     kva.block_table = pt->block_table;
+    kva.slots = P.slots;
 
     ap.qkv = P.qkv;
     ap.o = P.a;

@@ -155,6 +155,7 @@ struct KvAppend {            // where the QKV epilogue writes keys and values
     const int32_t* block_table;
     const int32_t* seq_lens;  // decode: slot = seq_lens[b]
     const int32_t* active;    // decode: per-row flag
+    const int32_t* slots;     // prefill: [M] page * 64 + slot of every row, -1 if the page table does not cover it
 };
 
 struct GemvArgs {
@@ -280,6 +281,8 @@ hipError_t launch_quantize(int wdtype, const float* w, int64_t N, int64_t K, int
 hipError_t launch_ln_rows(int wdtype, const float* x, const void* g, const void* b, float eps, int M, int d,
                           void* out, hipStream_t st);
 hipError_t launch_gemm(int wdtype, int epi, const GemmArgs& a, hipStream_t st);
+bool gemm_large_wanted(int M, int N);  // bf16 weights: enough tiles for gemm_large_kernel
+hipError_t launch_gemm_large(int epi, const GemmArgs& a, hipStream_t st);
 hipError_t launch_attn_prefill(int wdtype, const AttnPrefillArgs& a, int total_tiles, hipStream_t st);
 int prefill_tile_rows(int wdtype);  // queries per prefill-attention workgroup
 // Attention without a mask (every query sees every key of its sequence), bf16; the
@@ -289,6 +292,9 @@ hipError_t launch_gather_rows(const float* x, int d, const SeqTable& seqs, float
 hipError_t launch_advance(int32_t* tokens, int32_t* positions, int32_t* seq_lens, int32_t* sampled,
                           int32_t* remaining, int32_t stop_token, bool retire_on_stop, int32_t* history,
                           int32_t* step_counter, int max_steps, int B, hipStream_t st);
+// slots[m] of every packed row (KvAppend::slots), and count[0 .. n_count) = 0.
+hipError_t launch_prefill_setup(const SeqTable& seqs, const int32_t* block_table, int max_pages, int n_pages, int M,
+                                int32_t* slots, uint32_t* count, size_t n_count, hipStream_t st);
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st);
 hipError_t launch_bgemm(int wdtype, int epi, const BgemmArgs& a, hipStream_t st);
 int bgemm_splits(int wdtype, int N, int K, bool ln);

@@ -1,6 +1,7 @@
 // Small kernels around the hot path: token+position embedding (with the
 // per-row activity flag every later kernel reads), LayerNorm over packed rows
 // (prefill), row gathers, the next-token sampler and the weight quantiser.
+#include <algorithm>
 #include <climits>
 
 #include "ftts_internal.hpp"
@@ -168,6 +169,41 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st) {
     const int blocks = (int)((n + 255) / 256 < 1024 ? (n + 255) / 256 : 1024);
     hipLaunchKernelGGL(fill_u32_kernel, dim3(blocks > 0 ? blocks : 1), dim3(256), 0, st, p, n, v);
+    return hipGetLastError();
+}
+
+// ---- prefill bookkeeping: KV slot of every packed row, split-K counters ---------------------------
+// A row's slot is physical page * 64 + slot in the page (pages stay below 2^25:
+// a page of one layer is at least 32 KB), or -1.
+__global__ __launch_bounds__(256) void prefill_setup_kernel(SeqTable seqs, const int32_t* block_table, int max_pages,
+                                                            int n_pages, int M, int32_t* slots, uint32_t* count,
+                                                            size_t n_count) {
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+    for (size_t i = i0; i < n_count; i += step) count[i] = 0u;
+    for (size_t i = i0; i < (size_t)M; i += step) {
+        const int m = (int)i;
+        int lo = 0, hi = seqs.n - 1;  // the sequence holding row m: cu[sq] <= m < cu[sq + 1]
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (seqs.cu[mid] <= m) lo = mid;
+            else hi = mid - 1;
+        }
+        const int t = m - seqs.cu[lo], page = t / kPage;
+        int phys = -1;
+        if (page < max_pages) {
+            phys = block_table[(size_t)lo * max_pages + page];
+            if (phys < 0 || phys >= n_pages) phys = -1;
+        }
+        slots[m] = phys < 0 ? -1 : phys * kPage + t % kPage;
+    }
+}
+
+hipError_t launch_prefill_setup(const SeqTable& seqs, const int32_t* block_table, int max_pages, int n_pages, int M,
+                                int32_t* slots, uint32_t* count, size_t n_count, hipStream_t st) {
+    const size_t n = std::max((size_t)M, n_count);
+    const int blocks = (int)std::min<size_t>((n + 255) / 256, 1024);
+    hipLaunchKernelGGL(prefill_setup_kernel, dim3(std::max(blocks, 1)), dim3(256), 0, st, seqs, block_table, max_pages,
+                       n_pages, M, slots, count, n_count);
     return hipGetLastError();
 }
 
