@@ -226,33 +226,6 @@ size_t decode_bytes(const ftts_config& c, int B, DecodeWs* out, char* base) {
     return off;
 }
 
-// Split-K scratch of the prefill GEMMs for any row count up to M: the largest
-// S * rows * N partial buffer and the largest tile count (the split depends on
-// the row count, and a smaller call may split where a larger one does not).
-void gemm_scratch(const ftts_config& c, int M, size_t* part_floats, size_t* counters) {
-    size_t pf = 0, cn = 0;
-    if (c.wdtype != FTTS_F32 && M > 0) {
-        const int d = c.d_model, F = c.d_ff;
-        const int NK[4][2] = {{3 * d, d}, {d, d}, {F, d}, {d, F}};
-        for (int step = 64;; step += 64) {
-            const int rows = std::min(step, M);
-            bool split = false;
-            for (const auto& t : NK) {
-                const GemmPlan p = gemm_plan(rows, t[0], t[1]);
-                if (p.splits > 1) {
-                    split = true;
-                    // partial tiles are whole (64 mt) x 128 tiles, past the matrix edges too
-                    pf = std::max(pf, (size_t)p.splits * p.tiles_m * p.tiles_n * (64 * p.mt) * 128);
-                    cn = std::max(cn, (size_t)p.tiles_m * p.tiles_n);
-                }
-            }
-            if (rows >= M || !split) break;  // more rows only add tiles
-        }
-    }
-    *part_floats = pf;
-    *counters = cn;
-}
-
 size_t prefill_bytes(const ftts_config& c, int B, int M, PrefillWs* out, char* base) {
     const size_t e = act_bytes(c);
     size_t off = mega_bytes(nullptr, nullptr);
@@ -263,10 +236,10 @@ size_t prefill_bytes(const ftts_config& c, int B, int M, PrefillWs* out, char* b
     char* h = take((size_t)M * c.d_ff * e);
     char* xl = take((size_t)B * c.d_model * 4);
     char* act = take((size_t)B * 4);
-    size_t pf, cn;
-    gemm_scratch(c, M, &pf, &cn);
-    char* part = pf ? take(pf * 4) : nullptr;
-    char* count = cn ? take(cn * 4) : nullptr;
+    // split-K scratch for any row count (a smaller call may split where a larger one does not)
+    const bool mfma = c.wdtype != FTTS_F32 && M > 0;
+    char* part = mfma ? take(kGemmPartFloats * 4) : nullptr;
+    char* count = mfma ? take(kGemmSplitTiles * 4) : nullptr;
     char* slots = take((size_t)M * 4);
     if (out)
         *out = PrefillWs{(float*)x,   a,     qkv, h, (float*)xl, (int32_t*)act, (float*)part, (uint32_t*)count,
@@ -731,9 +704,8 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
         as.x = P.x;
         if ((e = launch_assemble_prefix(c.wdtype, as, Mi, st)) != hipSuccess) return hip_fail(e, "input assembly");
     }
-    size_t pf = 0, cn = 0;
-    if (P.count) gemm_scratch(c, Mi, &pf, &cn);
-    if ((e = launch_prefill_setup(seqs, pt->block_table, pt->max_pages, kv->n_pages, Mi, P.slots, P.count, cn, st)) !=
+    if ((e = launch_prefill_setup(seqs, pt->block_table, pt->max_pages, kv->n_pages, Mi, P.slots, P.count,
+                                  P.count ? kGemmSplitTiles : 0, st)) !=
         hipSuccess)
         return hip_fail(e, "prefill setup");
 
@@ -752,6 +724,8 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
     ap.n_head = c.n_head;
     ap.seqs = seqs;
 
+    const GemmPlan p_qkv = gemm_plan(c.wdtype, Mi, 3 * d, d), p_out = gemm_plan(c.wdtype, Mi, d, d);
+    const GemmPlan p_fc1 = gemm_plan(c.wdtype, Mi, F, d), p_fc2 = gemm_plan(c.wdtype, Mi, d, F);
     for (int l = 0; l < c.n_layer; ++l) {
         const ftts_layer& L = w->layers[l];
         if ((e = launch_ln_rows(c.wdtype, P.x, L.ln1_g, L.ln1_b, c.ln_eps, Mi, d, P.a, st)) != hipSuccess)
@@ -771,7 +745,7 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
         g.kv = kva;
         g.kv.layer = l;
         g.seqs = seqs;
-        if ((e = launch_gemm(c.wdtype, EPI_QKV, g, st)) != hipSuccess) return hip_fail(e, "qkv gemm");
+        if ((e = launch_gemm(c.wdtype, EPI_QKV, g, p_qkv, st)) != hipSuccess) return hip_fail(e, "qkv gemm");
         if ((e = launch_attn_prefill(c.wdtype, ap, ap.tiles_cu[B], st)) != hipSuccess)
             return hip_fail(e, "prefill attention");
         g.w = L.out.w;
@@ -781,7 +755,7 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
         g.N = d;
         g.K = d;
         g.out = P.x;
-        if ((e = launch_gemm(c.wdtype, EPI_RESID, g, st)) != hipSuccess) return hip_fail(e, "out gemm");
+        if ((e = launch_gemm(c.wdtype, EPI_RESID, g, p_out, st)) != hipSuccess) return hip_fail(e, "out gemm");
         if ((e = launch_ln_rows(c.wdtype, P.x, L.ln2_g, L.ln2_b, c.ln_eps, Mi, d, P.a, st)) != hipSuccess)
             return hip_fail(e, "ln2");
         g.w = L.fc1.w;
@@ -791,7 +765,7 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
         g.N = F;
         g.K = d;
         g.out = P.h;
-        if ((e = launch_gemm(c.wdtype, EPI_GELU, g, st)) != hipSuccess) return hip_fail(e, "fc1 gemm");
+        if ((e = launch_gemm(c.wdtype, EPI_GELU, g, p_fc1, st)) != hipSuccess) return hip_fail(e, "fc1 gemm");
         g.a = P.h;
         g.w = L.fc2.w;
         g.scale = (const uint16_t*)L.fc2.scale;
@@ -800,7 +774,7 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
         g.N = d;
         g.K = F;
         g.out = P.x;
-        if ((e = launch_gemm(c.wdtype, EPI_RESID, g, st)) != hipSuccess) return hip_fail(e, "fc2 gemm");
+        if ((e = launch_gemm(c.wdtype, EPI_RESID, g, p_fc2, st)) != hipSuccess) return hip_fail(e, "fc2 gemm");
     }
     // A new generation starts: clear the persistent step's control words and
     // exchange buffers (epoch 0 never matches a live epoch).
@@ -902,28 +876,6 @@ int check_dit_config(const ftts_dit_config* c) {
     return FTTS_OK;
 }
 
-// Split-K scratch of the step's six GEMM shapes at M = 2T rows, maximised over every
-// row count up to M (a smaller call may split where a larger one does not).
-void dit_gemm_scratch(const ftts_dit_config& c, int M, size_t* part_floats, size_t* counters) {
-    const int d = c.d_model, F = c.d_ff, Kin = c.n_mel + c.d_cond;
-    const int NK[6][2] = {{d, Kin}, {3 * d, d}, {d, d}, {F, d}, {d, F}, {c.n_mel, d}};
-    size_t pf = 0, cn = 0;
-    for (int r = 64;; r += 64) {
-        const int rows = std::min(r, M);
-        for (const auto& t : NK) {
-            const GemmPlan p = gemm_plan(rows, t[0], t[1]);
-            if (p.splits > 1) {
-                // partial tiles are whole (64 mt) x 128 tiles, past the matrix edges too
-                pf = std::max(pf, (size_t)p.splits * p.tiles_m * p.tiles_n * (64 * p.mt) * 128);
-                cn = std::max(cn, (size_t)p.tiles_m * p.tiles_n);
-            }
-        }
-        if (rows >= M) break;
-    }
-    *part_floats = pf;
-    *counters = cn;
-}
-
 size_t dit_bytes(const ftts_dit_config& c, int T, DitWs* out, char* base) {
     const size_t M = 2 * (size_t)T, d = c.d_model, Kin = (size_t)c.n_mel + c.d_cond;
     size_t off = 0;
@@ -935,11 +887,11 @@ size_t dit_bytes(const ftts_dit_config& c, int T, DitWs* out, char* base) {
     char* vel = take(M * (size_t)c.n_mel * 4);
     char* u = take(d * 4);
     char* e = take(d * 4);
-    size_t pf, cn;
-    dit_gemm_scratch(c, (int)M, &pf, &cn);
-    char* part = pf ? take(pf * 4) : nullptr;
-    char* count = cn ? take(cn * 4) : nullptr;
-    if (out) *out = DitWs{(float*)h, a, qkv, f, (float*)vel, (float*)u, (float*)e, (float*)part, (uint32_t*)count, cn};
+    char* part = take(kGemmPartFloats * 4);
+    char* count = take(kGemmSplitTiles * 4);
+    if (out)
+        *out = DitWs{(float*)h, a, qkv, f, (float*)vel, (float*)u, (float*)e, (float*)part, (uint32_t*)count,
+                     kGemmSplitTiles};
     return off;
 }
 
@@ -1047,7 +999,8 @@ int ftts_dit_step(const ftts_dit_weights* w, const float* x, const void* cond, c
     pa.n_count = W.n_count;
     if ((e = launch_dit_prepare(pa, st)) != hipSuccess) return hip_fail(e, "step inputs");
     // h = [x | c] W_in^T + b_in + e(t)
-    if ((e = launch_gemm(FTTS_BF16, EPI_RESID, dit_gemm(w->in, W.a, M, d, Kin, W.h, W), st)) != hipSuccess)
+    if ((e = launch_gemm(FTTS_BF16, EPI_RESID, dit_gemm(w->in, W.a, M, d, Kin, W.h, W),
+                         gemm_plan(FTTS_BF16, M, d, Kin), st)) != hipSuccess)
         return hip_fail(e, "input projection");
 
     AttnPrefillArgs ap{};
@@ -1063,25 +1016,28 @@ int ftts_dit_step(const ftts_dit_weights* w, const float* x, const void* cond, c
         ap.seqs.cu[B + b + 1] = T + ap.seqs.cu[b + 1];
     }
 
+    const GemmPlan p_qkv = gemm_plan(FTTS_BF16, M, 3 * d, d), p_out = gemm_plan(FTTS_BF16, M, d, d);
+    const GemmPlan p_fc1 = gemm_plan(FTTS_BF16, M, F, d), p_fc2 = gemm_plan(FTTS_BF16, M, d, F);
     for (int l = 0; l < c.n_layer; ++l) {
         const ftts_layer& L = w->layers[l];
         if ((e = launch_ln_rows(FTTS_BF16, W.h, L.ln1_g, L.ln1_b, c.ln_eps, M, d, W.a, st)) != hipSuccess)
             return hip_fail(e, "ln1");
-        if ((e = launch_gemm(FTTS_BF16, EPI_STORE, dit_gemm(L.qkv, W.a, M, 3 * d, d, W.qkv, W), st)) != hipSuccess)
+        if ((e = launch_gemm(FTTS_BF16, EPI_STORE, dit_gemm(L.qkv, W.a, M, 3 * d, d, W.qkv, W), p_qkv, st)) != hipSuccess)
             return hip_fail(e, "qkv gemm");
         if ((e = launch_attn_full_bf16(ap, st)) != hipSuccess) return hip_fail(e, "attention");
-        if ((e = launch_gemm(FTTS_BF16, EPI_RESID, dit_gemm(L.out, W.a, M, d, d, W.h, W), st)) != hipSuccess)
+        if ((e = launch_gemm(FTTS_BF16, EPI_RESID, dit_gemm(L.out, W.a, M, d, d, W.h, W), p_out, st)) != hipSuccess)
             return hip_fail(e, "out gemm");
         if ((e = launch_ln_rows(FTTS_BF16, W.h, L.ln2_g, L.ln2_b, c.ln_eps, M, d, W.a, st)) != hipSuccess)
             return hip_fail(e, "ln2");
-        if ((e = launch_gemm(FTTS_BF16, EPI_GELU, dit_gemm(L.fc1, W.a, M, F, d, W.f, W), st)) != hipSuccess)
+        if ((e = launch_gemm(FTTS_BF16, EPI_GELU, dit_gemm(L.fc1, W.a, M, F, d, W.f, W), p_fc1, st)) != hipSuccess)
             return hip_fail(e, "fc1 gemm");
-        if ((e = launch_gemm(FTTS_BF16, EPI_RESID, dit_gemm(L.fc2, W.f, M, d, F, W.h, W), st)) != hipSuccess)
+        if ((e = launch_gemm(FTTS_BF16, EPI_RESID, dit_gemm(L.fc2, W.f, M, d, F, W.h, W), p_fc2, st)) != hipSuccess)
             return hip_fail(e, "fc2 gemm");
     }
     if ((e = launch_ln_rows(FTTS_BF16, W.h, w->lnf_g, w->lnf_b, c.ln_eps, M, d, W.a, st)) != hipSuccess)
         return hip_fail(e, "final layer norm");
-    if ((e = launch_gemm(FTTS_BF16, EPI_RESID, dit_gemm(w->mel, W.a, M, c.n_mel, d, W.vel, W), st)) != hipSuccess)
+    if ((e = launch_gemm(FTTS_BF16, EPI_RESID, dit_gemm(w->mel, W.a, M, c.n_mel, d, W.vel, W),
+                         gemm_plan(FTTS_BF16, M, c.n_mel, d), st)) != hipSuccess)
         return hip_fail(e, "mel projection");
     if ((e = launch_dit_guide(W.vel, T, c.n_mel, cfg_w, dt, x, x_out, v_out, st)) != hipSuccess)
         return hip_fail(e, "guidance");

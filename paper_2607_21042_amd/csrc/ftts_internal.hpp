@@ -234,14 +234,18 @@ struct GemmArgs {
     void* out;               // STORE/QKV/GELU: [M][N] activation dtype; RESID: fp32 [M][N] in place
     KvAppend kv;             // QKV epilogue (prefill form: slot = position within the sequence)
     SeqTable seqs;
-    float* part;             // split K: [S][M][N] fp32 partial tiles
+    float* part;             // split K: [S] fp32 partial tiles of whole 64 x bn blocks
     uint32_t* count;         // split K: per-tile arrival counters, zero between calls
 };
-struct GemmPlan {            // 16-bit-mode prefill GEMM launch shape
-    int mt;                  // 64-row blocks per tile (1 or 2)
-    int tiles_m, tiles_n, splits;
+struct GemmPlan {      // 16-bit-mode GEMM launch shape
+    int rows_large;    // rows 0 .. rows_large - 1 take gemm_large_kernel (0: none) in tiles of
+    int mt, nt;        //   64 mt rows and 128 nt columns;
+    int bn, splits;    // the rest take gemm_small_kernel: tiles of 64 rows and bn columns, K in `splits` slices
 };
-GemmPlan gemm_plan(int M, int N, int K);
+GemmPlan gemm_plan(int wdtype, int M, int N, int K);
+// A plan that splits K has at most this many tiles, and workgroups (tiles x slices).
+constexpr int kGemmSplitTiles = 256, kGemmSplitGroups = 512;
+constexpr size_t kGemmPartFloats = (size_t)kGemmSplitGroups * 64 * 128;  // GemmArgs::part (GemmArgs::count: kGemmSplitTiles)
 
 struct AttnPrefillArgs {
     const void* qkv;         // [M][3d] activation dtype
@@ -280,9 +284,9 @@ hipError_t launch_quantize(int wdtype, const float* w, int64_t N, int64_t K, int
                            uint16_t* scales, uint16_t* zeros, hipStream_t st);
 hipError_t launch_ln_rows(int wdtype, const float* x, const void* g, const void* b, float eps, int M, int d,
                           void* out, hipStream_t st);
-hipError_t launch_gemm(int wdtype, int epi, const GemmArgs& a, hipStream_t st);
-bool gemm_large_wanted(int M, int N);  // bf16 weights: enough tiles for gemm_large_kernel
-hipError_t launch_gemm_large(int epi, const GemmArgs& a, hipStream_t st);
+hipError_t launch_gemm(int wdtype, int epi, const GemmArgs& a, const GemmPlan& p, hipStream_t st);  // p unused in fp32
+hipError_t launch_gemm_large(int epi, const GemmArgs& a, int mt, int nt, hipStream_t st);
+hipError_t launch_gemm_small(int wdtype, int epi, const GemmArgs& a, int bn, int splits, hipStream_t st);
 hipError_t launch_attn_prefill(int wdtype, const AttnPrefillArgs& a, int total_tiles, hipStream_t st);
 int prefill_tile_rows(int wdtype);  // queries per prefill-attention workgroup
 // Attention without a mask (every query sees every key of its sequence), bf16; the

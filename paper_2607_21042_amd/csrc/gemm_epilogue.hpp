@@ -46,47 +46,48 @@ __device__ __forceinline__ void load_bias4(const void* bias, int n, float* out) 
 }
 
 // KV slots (page * 64 + slot, or -1) of the rows that store_block_bf16 writes for this lane.
-template <int EPI>
-__device__ __forceinline__ void load_slots(const GemmArgs& a, int m0, int n0, int lane, int (&slots)[4]) {
+template <int EPI, int NT>
+__device__ __forceinline__ void load_slots(const GemmArgs& a, int m0, int n0, int lane, int (&slots)[2 * NT]) {
     if (EPI != EPI_QKV || n0 < a.kv.d_model) return;
 #pragma unroll
-    for (int it = 0; it < 4; ++it) slots[it] = a.kv.slots[min(m0 + (lane >> 3) + 8 * it, a.M - 1)];
+    for (int it = 0; it < 2 * NT; ++it) slots[it] = a.kv.slots[min(m0 + (lane + 64 * it) / (4 * NT), a.M - 1)];
 }
 
-// A wave's 32 x 64 block of bf16 outputs (pk[n][g]: the lane's four columns
+// A wave's 32 x (32 NT) block of bf16 outputs (pk[n][g]: the lane's four columns
 // 32 n + 8 g + 4 fh ..) to rows m0.. and columns n0.. of a.out, through 4 KB of
-// the wave's LDS so that a row's 128 bytes go out in 16-byte pieces of
-// consecutive lanes; for q/k/v the keys and values (64 columns are one head) also
-// go into their KV pages.  Pieces are XOR-swizzled by row, and the halves of a
-// piece by bit 3 of the row, so that neither the 8-byte writes nor the 16-byte
-// reads collide in banks.
-// The KV slots of the rows come in registers (load_slots), read before the first
-// store: a load issued among the stores would wait for all of them.
-template <int EPI>
-__device__ __forceinline__ void store_block_bf16(const GemmArgs& a, const uint2 (&pk)[2][4], const int (&slots)[4],
+// the wave's LDS (rows of 128 bytes) so that a row's bytes go out in 16-byte pieces
+// of consecutive lanes; for q/k/v the keys and values (a block's columns belong to
+// one head) also go into their KV pages.  Pieces are XOR-swizzled by row, and the
+// halves of a piece by bit 3 of the row, so that neither the 8-byte writes nor the
+// 16-byte reads collide in banks.  The KV slots of the rows come in registers
+// (load_slots), read before the first store: a load issued among the stores would
+// wait for all of them.
+template <int EPI, int NT>
+__device__ __forceinline__ void store_block_bf16(const GemmArgs& a, const uint2 (&pk)[NT][4], const int (&slots)[2 * NT],
                                                  char* eb, int m0, int n0, int lane) {
     const int fr = lane & 31, fh = lane >> 5;
 #pragma unroll
-    for (int n = 0; n < 2; ++n)
+    for (int n = 0; n < NT; ++n)
 #pragma unroll
         for (int g = 0; g < 4; ++g)
             *reinterpret_cast<uint2*>(eb + fr * 128 + (((n * 4 + g) ^ (fr & 7)) << 4) + ((fh ^ ((fr >> 3) & 1)) << 3)) =
                 pk[n][g];
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     uint16_t* out = reinterpret_cast<uint16_t*>(a.out);
-    const int d = a.kv.d_model, q = lane & 7, n = n0 + q * 8;
-    const bool is_kv = EPI == EPI_QKV && n0 >= d;  // uniform: 64 columns are one head
+    constexpr int PR = 4 * NT;  // 16-byte pieces of a row
+    const int d = a.kv.d_model;
+    const bool is_kv = EPI == EPI_QKV && n0 >= d;  // uniform over the wave
 #pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        const int rl = (lane >> 3) + 8 * it, m = m0 + rl;
+    for (int it = 0; it < 2 * NT; ++it) {
+        const int j = lane + 64 * it, rl = j / PR, q = j % PR, m = m0 + rl, n = n0 + q * 8;
         uint4 v = *reinterpret_cast<const uint4*>(eb + rl * 128 + ((q ^ (rl & 7)) << 4));
-        if (it & 1) v = make_uint4(v.z, v.w, v.x, v.y);
+        if ((rl >> 3) & 1) v = make_uint4(v.z, v.w, v.x, v.y);
         if (m < a.M && n < a.N) {
             *reinterpret_cast<uint4*>(out + (size_t)m * a.N + n) = v;
             if (is_kv && slots[it] >= 0) {
-                const int kvsel = n0 >= 2 * d, r = n0 - d - kvsel * d, s = slots[it];
+                const int kvsel = n >= 2 * d, r = n - d - kvsel * d, s = slots[it];
                 const size_t off = kv_offset(a.kv.layer, a.kv.n_pages, s / kPage, kvsel, a.kv.n_head, r / kHeadDim,
-                                             s % kPage) + q * 8;
+                                             s % kPage) + r % kHeadDim;
                 *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(a.kv.base) + off) = v;
             }
         }
