@@ -267,17 +267,24 @@ hipError_t launch_assemble_prefix(int wdtype, const AssembleArgs& a, int rows, h
 }
 
 // ---- sampler ------------------------------------------------------------------------------
-// One 256-thread workgroup per sequence; thread t holds the tempered logits of
-// indices t, t + 256, ... in registers.  Order is by (value, index): the larger
+// One 1024-thread workgroup per sequence; thread t holds the tempered logits of
+// indices t, t + 1024, ... in registers.  Order is by (value, index): the larger
 // value first, the lower index on ties.  NaN logits count as -inf.
 //
-// Top-k without k sequential block reductions: each wave finds the k-th largest
-// of its 64 lane maxima, t_w; at least k entries are >= t_w, so with t = max_w t_w
-// every one of the k best entries is >= t.  The entries >= t (typically a few
-// times k) are compacted into LDS and each is ranked by counting the candidates
-// that beat it; ranks below k fill the ordered top-k list.  Rows with more than
-// kSampCand candidates (massive exact ties) take k rounds of block argmax instead.
-constexpr int kSampThreads = 256, kSampWaves = kSampThreads / kWave, kSampPer = 64;  // vocab <= 16384
+// Top-k without k sequential block reductions.  If t is the k-th largest of the 256
+// maxima over groups of four lanes, at least k entries are >= t, so every one of the k
+// best is, and few others are (about 32 in all for k = 30, whatever the row's length).
+// t is found by counting, one thread per group maximum; the entries >= t are
+// collected in LDS as 64-bit keys that sort by (value, index), each is ranked by
+// counting the keys above it, and ranks below k fill the ordered top-k list.  Rows
+// with more than kSampCand candidates (massive exact ties) take k rounds of block
+// argmax instead.
+//
+// A row is 33 KB, so the kernel is bound by its chain of short steps: with 256 threads
+// (64 entries each, 33 divisions of them in use, a per-wave threshold that let about
+// 180 candidates through, ranked one LDS read at a time) 32 rows of 8194 took 23.7 us
+// at k = 30; now 10.9 us.
+constexpr int kSampThreads = 1024, kSampWaves = kSampThreads / kWave, kSampPer = 16;  // vocab <= 16384
 constexpr int kSampCand = 1024;
 
 __device__ __forceinline__ bool beats(float v, int i, float bv, int bi) {
@@ -314,7 +321,7 @@ __device__ __forceinline__ void wave_best(float& v, int& i) {
 
 // Best untaken entry of this lane (indices increase with the slot, so the
 // first of equal values wins).
-__device__ __forceinline__ void lane_best(const float (&z)[kSampPer], uint64_t taken, float& bv, int& bi) {
+__device__ __forceinline__ void lane_best(const float (&z)[kSampPer], uint32_t taken, float& bv, int& bi) {
     bv = -INFINITY;
     bi = INT_MAX;
 #pragma unroll
@@ -347,13 +354,14 @@ __device__ __forceinline__ void block_best(float& v, int& i, float* rv, int* ri)
 __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logits, int V, float temperature,
                                                               int top_k, float top_p, const float* uniforms,
                                                               const int32_t* active, int32_t* out) {
-    __shared__ float cand_v[kSampCand];
-    __shared__ int cand_i[kSampCand];
+    __shared__ __attribute__((aligned(16))) float s_gm[kSampThreads / 4];  // group maxima
+    __shared__ __attribute__((aligned(16))) uint64_t s_key[kSampCand + 8];
     __shared__ float selv[FTTS_MAX_TOP_K];
     __shared__ int seli[FTTS_MAX_TOP_K];
     __shared__ float rv[kSampWaves];
     __shared__ int ri[kSampWaves];
-    __shared__ int s_cnt[kSampWaves];
+    __shared__ int s_cnt;
+    __shared__ float s_t;
     const int b = blockIdx.x, tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
     const float* row = logits + (size_t)b * V;
     const bool greedy = top_k == 1;
@@ -364,6 +372,7 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
         const int i = tid + kSampThreads * j;
         z[j] = i < V ? row[i] : -INFINITY;
     }
+    if (tid == 0) s_cnt = 0;
     const float u = greedy ? 0.f : uniforms[b];
     if (active && !active[b]) {
         if (tid == 0) out[b] = -1;
@@ -371,6 +380,7 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
     }
 #pragma unroll
     for (int j = 0; j < kSampPer; ++j) {
+        if (kSampThreads * j >= V) continue;  // uniform: slots past the row stay -inf
         const float v = greedy ? z[j] : z[j] / temperature;
         z[j] = v != v ? -INFINITY : v;
     }
@@ -382,61 +392,62 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
         if (tid == 0) out[b] = bi < V ? bi : 0;
         return;
     }
-    // wave threshold: the k-th largest lane maximum (ties: lower lane first)
     float lm = -INFINITY;
 #pragma unroll
     for (int j = 0; j < kSampPer; ++j) lm = fmaxf(lm, z[j]);
-    int rank = 0;
-#pragma unroll
-    for (int l = 0; l < kWave; ++l) {
-        const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lm), l));
-        rank += (o > lm || (o == lm && l < lane)) ? 1 : 0;
+    {
+        const float gm = group_max<4>(lm);
+        if ((lane & 3) == 0) s_gm[tid >> 2] = gm;
     }
-    const uint64_t hit = __ballot(rank == top_k - 1);
-    const float tw = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lm), (int)__builtin_ctzll(hit)));
-    if (lane == 0) rv[wave] = tw;
     __syncthreads();
-    float t = rv[0];
-    for (int w = 1; w < kSampWaves; ++w) t = fmaxf(t, rv[w]);
-    // candidates: count, exclusive offsets (wave scan, then wave totals), compaction
-    int cnt = 0;
-#pragma unroll
-    for (int j = 0; j < kSampPer; ++j) cnt += z[j] >= t ? 1 : 0;
-    int incl = cnt;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int u = __shfl_up(incl, o, kWave);
-        incl += lane >= o ? u : 0;
+    if (tid < kSampThreads / 4) {
+        const float own = s_gm[tid];
+        int gt = 0, ge = 0;
+        const float4* g4 = reinterpret_cast<const float4*>(s_gm);
+#pragma unroll 8
+        for (int c = 0; c < kSampThreads / 16; ++c) {
+            const float4 o = g4[c];
+            gt += (o.x > own) + (o.y > own) + (o.z > own) + (o.w > own);
+            ge += (o.x >= own) + (o.y >= own) + (o.z >= own) + (o.w >= own);
+        }
+        if (gt < top_k && top_k <= ge) s_t = own;  // (every thread that writes holds the same value)
     }
-    if (lane == kWave - 1) s_cnt[wave] = incl;
     __syncthreads();
-    int off = incl - cnt, total = 0;
-    for (int w = 0; w < kSampWaves; ++w) {
-        off += w < wave ? s_cnt[w] : 0;
-        total += s_cnt[w];
-    }
-    if (total <= kSampCand) {
+    const float t = s_t;
+    if (lm >= t) {
 #pragma unroll
         for (int j = 0; j < kSampPer; ++j)
             if (z[j] >= t) {
-                cand_v[off] = z[j];
-                cand_i[off] = tid + kSampThreads * j;
-                ++off;
+                const int c = atomicAdd(&s_cnt, 1);
+                // larger value first, then lower index (+ 0.f: -0 ties with +0)
+                const uint32_t u = __float_as_uint(z[j] + 0.f), k = (u >> 31) ? ~u : u | 0x80000000u;
+                if (c < kSampCand) s_key[c] = ((uint64_t)k << 32) | (uint32_t)(0x7FFFFFFF - (tid + kSampThreads * j));
             }
+    }
+    __syncthreads();
+    const int total = s_cnt;
+    if (total <= kSampCand) {
+        if (tid < 8) s_key[total + tid] = 0;  // below every key, so that the ranking reads whole groups of 8
         __syncthreads();
         for (int c = tid; c < total; c += kSampThreads) {
-            const float cv = cand_v[c];
-            const int ci = cand_i[c];
+            const uint64_t own = s_key[c];
             int r = 0;
-            for (int c2 = 0; c2 < total; ++c2) r += beats(cand_v[c2], cand_i[c2], cv, ci) ? 1 : 0;
+            for (int c2 = 0; c2 < total; c2 += 8) {
+                uint64_t o[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = s_key[c2 + e];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) r += o[e] > own ? 1 : 0;
+            }
             if (r < top_k) {
-                selv[r] = cv;
-                seli[r] = ci;
+                const uint32_t k = (uint32_t)(own >> 32);
+                selv[r] = __uint_as_float((k >> 31) ? k & 0x7FFFFFFFu : ~k);
+                seli[r] = 0x7FFFFFFF - (int)(uint32_t)own;
             }
         }
         __syncthreads();
     } else {
-        uint64_t taken = 0;
+        uint32_t taken = 0;
         float bv;
         int bi;
         lane_best(z, taken, bv, bi);
@@ -449,7 +460,7 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
                 seli[r] = wi;
             }
             if (wi == bi && (wi - tid) % kSampThreads == 0) {  // this thread held the winner
-                taken |= 1ull << ((wi - tid) / kSampThreads);
+                taken |= 1u << ((wi - tid) / kSampThreads);
                 lane_best(z, taken, bv, bi);
             }
         }
