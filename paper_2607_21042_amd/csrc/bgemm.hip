@@ -26,7 +26,7 @@
 // step st from contiguous columns (bf16: k = h*16 + st*8 + i; W4A16: word
 // h*8+st), and the input operand uses the same map, so the dot product is
 // unchanged.
-#include "ftts_internal.hpp"
+#include "gemm_epilogue.hpp"
 
 namespace ftts {
 
@@ -96,11 +96,16 @@ __device__ __forceinline__ void load_chunk(const BgemmArgs& p, int n, int m, int
 // one run of RB = CPW * CB bytes; direct-to-LDS loads bring the runs in with
 // 16 lanes (or fewer) per run and several whole runs per 1 KB instruction, and
 // the products read their operands from LDS.  The 16-byte pieces of row r are
-// stored XOR-swizzled by r (piece p at slot p ^ (r % pieces)) so that the 32
-// rows of one operand read fall into different banks.
-typedef __attribute__((address_space(3))) char bgemm_lds_char;
-__device__ __forceinline__ void lds_dma16(const char* src, char* dst) {
-    __builtin_amdgcn_global_load_lds(src, (bgemm_lds_char*)dst, 16, 0, 0);
+// stored XOR-swizzled by the row (row_swizzle) so that the 32 rows of one operand
+// read fall into different banks.  The loads go through a buffer descriptor: one
+// offset per lane and instruction, the slice's column as the scalar offset, and rows
+// past the matrix or the batch read as zero, instead of a clamped 64-bit address per
+// lane and load.
+// The 16 lanes whose 16-byte reads share a cycle take 256 bytes: rows of 64 and 128
+// bytes share that window four and two at a time.
+template <int PIECES>
+__device__ __forceinline__ int row_swizzle(int r) {
+    return PIECES == 4 ? (r >> 2) & 3 : PIECES == 8 ? (r >> 1) & 7 : r & (PIECES - 1);
 }
 template <int WT, bool LN, int FT> struct WStageShape {
     static constexpr int RB = ChunksPerWave<WT, LN>::value * BChunk<WT>::CB;  // bytes per row
@@ -109,20 +114,19 @@ template <int WT, bool LN, int FT> struct WStageShape {
 };
 
 template <int WT, bool LN, int FT>
-__device__ __forceinline__ void stage_weights(const BgemmArgs& p, int n0, int cw0, int c1, char* dst) {
+__device__ __forceinline__ void stage_weights(const BgemmArgs& p, int n0, int cw0, char* dst) {
     using C = BChunk<WT>;
     using SH = WStageShape<WT, LN, FT>;
-    constexpr int PPC = C::CB / 16;  // pieces per chunk
+    constexpr int RPI = 1024 / SH::RB;  // rows per instruction
     const int lane = threadIdx.x & 63;
-    const size_t row_bytes = WT == FTTS_W4A16 ? (size_t)p.K / 2 : WT == FTTS_W8A16 ? (size_t)p.K : (size_t)p.K * 2;
-    const char* wb = reinterpret_cast<const char*>(p.w);
+    const int row_bytes = WT == FTTS_W4A16 ? p.K / 2 : WT == FTTS_W8A16 ? p.K : p.K * 2;
+    const char* base = reinterpret_cast<const char*>(p.w) + (size_t)n0 * row_bytes;
+    const int bytes = min(p.N - n0, FT * kBgemmFeat) * row_bytes;
+    const int r0 = lane / SH::PIECES;  // row of the first instruction; instruction i adds RPI i
 #pragma unroll
     for (int i = 0; i < SH::OPS; ++i) {
-        const int off = i * 1024 + lane * 16, r = off / SH::RB, q = (off % SH::RB) / 16;
-        const int pc = q ^ (r & (SH::PIECES - 1));                // the piece that lands in slot q
-        const int c = min(cw0 + pc / PPC, c1 - 1);                 // its chunk (past the slice: a repeat)
-        const int n = min(n0 + r, p.N - 1);
-        lds_dma16(wb + (size_t)n * row_bytes + (size_t)c * C::CB + (pc % PPC) * 16, dst + i * 1024);
+        const int r = i * RPI + r0, pc = (lane % SH::PIECES) ^ row_swizzle<SH::PIECES>(r);  // the piece that lands in this lane's slot
+        buffer_to_lds16(base, bytes, dst + i * 1024, (uint32_t)(r * row_bytes + pc * 16), cw0 * C::CB);
     }
 }
 
@@ -133,14 +137,14 @@ __device__ __forceinline__ void read_weights(const char* src, int fr, int h, int
     constexpr int NW = (int)(sizeof(ch.w) / 16), PPC = BChunk<WT>::CB / 16;
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
-        const int pc = j * PPC + h * NW + i, q = pc ^ (fr & (SH::PIECES - 1));
+        const int pc = j * PPC + h * NW + i, q = pc ^ row_swizzle<SH::PIECES>(fr);
         ch.w[i] = *reinterpret_cast<const uint4*>(src + fr * SH::RB + q * 16);
     }
 }
 
 // LayerNorm input staging: this wave's 32 fp32 rows over its CPW chunks, RBX bytes
 // a row, by the same 1 KB direct-to-LDS loads and the same XOR swizzle of 16-byte
-// pieces.  Rows past the batch repeat the last row (their outputs are zeroed).
+// pieces.  Rows past the batch read as zero.
 template <int WT> struct XStageShape {
     static constexpr int RBX = ChunksPerWave<WT, true>::value * BChunk<WT>::KC * 4;
     static constexpr int PIECES = RBX / 16, BYTES = kBgemmRows * RBX, OPS = BYTES / 1024;
@@ -148,17 +152,14 @@ template <int WT> struct XStageShape {
 };
 
 template <int WT>
-__device__ __forceinline__ void stage_x(const BgemmArgs& p, int cw0, int c1, char* dst) {
+__device__ __forceinline__ void stage_x(const BgemmArgs& p, int cw0, char* dst) {
     using SH = XStageShape<WT>;
-    constexpr int KC = BChunk<WT>::KC;
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, r0 = lane / SH::PIECES;
+    constexpr int RPI = 1024 / SH::RBX;
 #pragma unroll
     for (int i = 0; i < SH::OPS; ++i) {
-        const int off = i * 1024 + lane * 16, r = off / SH::RBX, q = (off % SH::RBX) / 16;
-        const int pc = q ^ (r & (SH::PIECES - 1));  // the piece that lands in slot q: columns pc*4 .. +3
-        const int c = min(cw0 + pc * 4 / KC, c1 - 1);
-        const float* src = p.ln_x + (size_t)min(r, p.B - 1) * p.K + (size_t)c * KC + (pc * 4) % KC;
-        lds_dma16(reinterpret_cast<const char*>(src), dst + i * 1024);
+        const int r = i * RPI + r0, pc = (lane % SH::PIECES) ^ row_swizzle<SH::PIECES>(r);  // columns pc*4 .. +3
+        buffer_to_lds16(p.ln_x, p.B * p.K * 4, dst + i * 1024, (uint32_t)(r * p.K * 4 + pc * 16), cw0 * BChunk<WT>::KC * 4);
     }
 }
 
@@ -171,18 +172,14 @@ template <int WT> struct AStageShape {
 };
 
 template <int WT>
-__device__ __forceinline__ void stage_act(const BgemmArgs& p, int cw0, int c1, char* dst) {
+__device__ __forceinline__ void stage_act(const BgemmArgs& p, int cw0, char* dst) {
     using SH = AStageShape<WT>;
-    constexpr int KC = BChunk<WT>::KC;
-    const int lane = threadIdx.x & 63;
-    const uint16_t* act = reinterpret_cast<const uint16_t*>(p.act);
+    const int lane = threadIdx.x & 63, r0 = lane / SH::PIECES;
+    constexpr int RPI = 1024 / SH::RBA;
 #pragma unroll
     for (int i = 0; i < SH::OPS; ++i) {
-        const int off = i * 1024 + lane * 16, r = off / SH::RBA, q = (off % SH::RBA) / 16;
-        const int pc = q ^ (r & (SH::PIECES - 1));  // columns pc*8 .. +7
-        const int c = min(cw0 + pc * 8 / KC, c1 - 1);
-        const uint16_t* src = act + (size_t)min(r, p.B - 1) * p.K + (size_t)c * KC + (pc * 8) % KC;
-        lds_dma16(reinterpret_cast<const char*>(src), dst + i * 1024);
+        const int r = i * RPI + r0, pc = (lane % SH::PIECES) ^ row_swizzle<SH::PIECES>(r);  // columns pc*8 .. +7
+        buffer_to_lds16(p.act, p.B * p.K * 2, dst + i * 1024, (uint32_t)(r * p.K * 2 + pc * 16), cw0 * BChunk<WT>::KC * 2);
     }
 }
 
@@ -190,7 +187,7 @@ __device__ __forceinline__ void stage_act(const BgemmArgs& p, int cw0, int c1, c
 template <int WT>
 __device__ __forceinline__ uint4 read_a8(const char* src, int fr, int kl) {
     using SH = AStageShape<WT>;
-    const int q = (kl >> 3) ^ (fr & (SH::PIECES - 1));
+    const int q = (kl >> 3) ^ row_swizzle<SH::PIECES>(fr);
     return *reinterpret_cast<const uint4*>(src + fr * SH::RBA + q * 16);
 }
 
@@ -198,7 +195,7 @@ __device__ __forceinline__ uint4 read_a8(const char* src, int fr, int kl) {
 template <int WT>
 __device__ __forceinline__ float4 read_x4(const char* src, int fr, int kl) {
     using SH = XStageShape<WT>;
-    const int q = (kl >> 2) ^ (fr & (SH::PIECES - 1));
+    const int q = (kl >> 2) ^ row_swizzle<SH::PIECES>(fr);
     return *reinterpret_cast<const float4*>(src + fr * SH::RBX + q * 16);
 }
 
@@ -254,7 +251,7 @@ __global__ __launch_bounds__(kBgemmThreads) void bgemm_kernel(const BgemmArgs p)
     __shared__ float s_mean[LN ? kBgemmRows : 1], s_rstd[LN ? kBgemmRows : 1];
     __shared__ __attribute__((aligned(1024))) char s_wt[kBgemmWaves][WStageShape<WT, LN, FT>::BYTES];
     int& s_last = *reinterpret_cast<int*>(s_wt[0]);  // used only after every product is formed
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int f = blockIdx.x, s = blockIdx.y, S = gridDim.y;
     const int n0 = f * FEAT;
     const int fr = lane & 31, h = lane >> 5;
@@ -299,11 +296,11 @@ __global__ __launch_bounds__(kBgemmThreads) void bgemm_kernel(const BgemmArgs p)
         }
     }
     // 3. every weight and input load of this wave: its chunks are c0 + wave * CPW + j
-    // (indices past the slice repeat its last chunk and are not used)
+    // (chunks past the slice hold other columns, or zero, and are not used)
     const int cw0 = c0 + wave * CPW;
-    stage_weights<WT, LN, FT>(p, n0, cw0, c1, s_wt[wave]);
-    if constexpr (LN) stage_x<WT>(p, cw0, c1, s_xs[wave]);
-    else stage_act<WT>(p, cw0, c1, s_xs[wave]);
+    stage_weights<WT, LN, FT>(p, n0, cw0, s_wt[wave]);
+    if constexpr (LN) stage_x<WT>(p, cw0, s_xs[wave]);
+    else stage_act<WT>(p, cw0, s_xs[wave]);
     C ch[CPW];
 #pragma unroll
     for (int j = 0; j < CPW; ++j) load_chunk<WT, LN>(p, n0 + fr, fr, h, min(cw0 + j, c1 - 1), ch[j]);
@@ -387,7 +384,7 @@ __global__ __launch_bounds__(kBgemmThreads) void bgemm_kernel(const BgemmArgs p)
                     const float t = (xs[e] - mean) * rstd * gs[e] + bs[e];
                     y[e] = live ? t : 0.f;
                 }
-                if (p.hidden && f == 0 && live) {  // feature tile 0 of each slice covers the slice's columns
+                if (p.hidden && f == 0 && live && cw0 + j < c1) {  // feature tile 0 of each slice covers the slice's columns
                     float4* hd = reinterpret_cast<float4*>(p.hidden + (size_t)fr * p.K + k0 + kl + 8 * i);
                     hd[0] = make_float4(y[0], y[1], y[2], y[3]);
                     hd[1] = make_float4(y[4], y[5], y[6], y[7]);
