@@ -90,28 +90,39 @@ __global__ __launch_bounds__(256) void ln_rows_kernel(const float* x, const void
         st_act<F32>(out, r * d + k, (xr[k] - mean) * rstd * ld_act<F32>(g, k) + ld_act<F32>(bb, k));
 }
 
-// One wave per row for rows of up to 2048 columns that split into float4 lanes:
-// the row stays in registers, both reductions are cross-lane, no barriers.
-template <bool F32>
+// One wave per row for rows of up to 2048 columns that split into float4 lanes (N per
+// lane): the row stays in registers, both reductions are cross-lane, no barriers.  Short
+// launches are bound by their dependent loads, so the gains and biases are requested
+// with the row (bf16; after the reductions they cost another trip to memory: 256 x 1280
+// took 4.7 us a launch in a prefill, now see launch_ln_rows).
+template <bool F32, int N>
 __global__ __launch_bounds__(256) void ln_rows_wave_kernel(const float* x, const void* g, const void* bb, float eps,
                                                            int M, int d, void* out) {
-    constexpr int NMAX = 8;  // float4 per lane: d <= 64 * 4 * 8
     const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (r >= M) return;
     const float4* xr = reinterpret_cast<const float4*>(x + (size_t)r * d);
     const int n4 = d / 4;
-    float4 v[NMAX];
+    float4 v[N];
+    uint2 gw[F32 ? 1 : N], bw[F32 ? 1 : N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = xr[min(lane + 64 * i, n4 - 1)];
+    if constexpr (!F32) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            gw[i] = reinterpret_cast<const uint2*>(g)[min(lane + 64 * i, n4 - 1)];
+            bw[i] = reinterpret_cast<const uint2*>(bb)[min(lane + 64 * i, n4 - 1)];
+        }
+    }
     float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < NMAX; ++i) {
-        const int j = lane + 64 * i;
-        v[i] = j < n4 ? xr[j] : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int i = 0; i < N; ++i) {
+        if (lane + 64 * i >= n4) v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
     }
     const float mean = wave_sum(s) / (float)d;
     float q = 0.f;
 #pragma unroll
-    for (int i = 0; i < NMAX; ++i) {
+    for (int i = 0; i < N; ++i) {
         if (lane + 64 * i < n4) {
             const float a = v[i].x - mean, b = v[i].y - mean, c = v[i].z - mean, e = v[i].w - mean;
             q = fmaf(a, a, fmaf(b, b, fmaf(c, c, fmaf(e, e, q))));
@@ -119,7 +130,7 @@ __global__ __launch_bounds__(256) void ln_rows_wave_kernel(const float* x, const
     }
     const float rstd = 1.0f / sqrtf(wave_sum(q) / (float)d + eps);
 #pragma unroll
-    for (int i = 0; i < NMAX; ++i) {
+    for (int i = 0; i < N; ++i) {
         const int j = lane + 64 * i;
         if (j < n4) {
             const float xs[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
@@ -130,9 +141,7 @@ __global__ __launch_bounds__(256) void ln_rows_wave_kernel(const float* x, const
                                 (xs[k] - mean) * rstd * ld_act<F32>(g, 4 * j + k) + ld_act<F32>(bb, 4 * j + k));
             } else {
                 // four bf16 gains, biases and outputs per 8-byte access (rows of d % 4 == 0)
-                const uint2 gw = reinterpret_cast<const uint2*>(g)[j];
-                const uint2 bw = reinterpret_cast<const uint2*>(bb)[j];
-                const uint32_t gs[2] = {gw.x, gw.y}, bs[2] = {bw.x, bw.y};
+                const uint32_t gs[2] = {gw[i].x, gw[i].y}, bs[2] = {bw[i].x, bw[i].y};
                 uint32_t o[2];
 #pragma unroll
                 for (int k = 0; k < 2; ++k) {
@@ -148,12 +157,19 @@ __global__ __launch_bounds__(256) void ln_rows_wave_kernel(const float* x, const
     }
 }
 
+template <bool F32, int N>
+static void ln_rows_wave(const float* x, const void* g, const void* b, float eps, int M, int d, void* out, hipStream_t st) {
+    if constexpr (N < 8) {
+        if (d > 256 * N) return ln_rows_wave<F32, N + 1>(x, g, b, eps, M, d, out, st);
+    }
+    hipLaunchKernelGGL((ln_rows_wave_kernel<F32, N>), dim3((M + 3) / 4), dim3(256), 0, st, x, g, b, eps, M, d, out);
+}
+
 hipError_t launch_ln_rows(int wdtype, const float* x, const void* g, const void* b, float eps, int M, int d,
                           void* out, hipStream_t st) {
     if (d % 4 == 0 && d <= 2048) {
-        const dim3 grid((M + 3) / 4);
-        if (wdtype == FTTS_F32) hipLaunchKernelGGL(ln_rows_wave_kernel<true>, grid, dim3(256), 0, st, x, g, b, eps, M, d, out);
-        else hipLaunchKernelGGL(ln_rows_wave_kernel<false>, grid, dim3(256), 0, st, x, g, b, eps, M, d, out);
+        if (wdtype == FTTS_F32) ln_rows_wave<true, 1>(x, g, b, eps, M, d, out, st);
+        else ln_rows_wave<false, 1>(x, g, b, eps, M, d, out, st);
         return hipGetLastError();
     }
     if (wdtype == FTTS_F32) hipLaunchKernelGGL(ln_rows_kernel<true>, dim3(M), dim3(256), 0, st, x, g, b, eps, d, out);
