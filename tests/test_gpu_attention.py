@@ -1,0 +1,66 @@
+"""GPU parity of the 16-bit attention at the edges of its tiles: sequence lengths
+on both sides of the 64-key tile, the 32-query and 128-query tiles and one and
+two rounds of the key split, with and without the mask, packed into a short grid
+(the keys of a query tile split over waves) and a wide one (at least 256
+workgroups of 128 queries).  Through the public calls; bars as in
+tests/helpers.py (bf16 storage: 3e-2 absolute on logits; DiT: its own).
+"""
+import numpy as np
+import pytest
+
+from oracle import dit as odit
+from oracle import gpt as ogpt
+from paper_2607_21042_amd import workload
+from tests import helpers
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 191, 193, 255, 256, 257, 320, 321]
+# (heads, lengths): 20 sequences give fewer than 256 tiles of 128 queries at 4 heads, more at 8
+SHORT, WIDE = (4, EDGES), (8, EDGES + EDGES[::-1])
+
+
+@pytest.mark.parametrize("n_head,lens", [SHORT, WIDE])
+def test_causal_attention_edges(n_head, lens):
+    """Two layers: the first attends with every row, the last with each prefix's
+    last row; the decode steps read both layers' cached keys and values."""
+    from paper_2607_21042_amd import ftts
+    lens = lens[:32]
+    shape = workload.ModelShape(n_layer=2, d_model=64 * n_head, n_head=n_head, d_head=64, d_ff=512, vocab=640)
+    assert (sum(-(-n // 128) for n in lens) * n_head >= 256) == (n_head == 8)
+    inputs = workload.bf16_weights(workload.master_weights(shape, seed=3))
+    dm = ftts.DeviceModel(inputs, shape, ftts.BF16)
+    rows = workload.prefix_embeddings(lens, shape.d_model, seed=17)
+    prefixes = np.split(rows, np.cumsum(lens)[:-1])
+    fed = workload.random_tokens(2, len(lens), shape.vocab, seed=5)
+    print(f"causal attention edges: {n_head} heads, {len(lens)} prefixes", flush=True)
+    res = helpers.run_gpu(dm, shape, prefixes, fed)
+    model = ogpt.GPT(helpers.oracle_weights(inputs, "bf16"), shape.n_head, shape.d_head)
+    for b in range(len(lens)):
+        last, dec = helpers.oracle_teacher_forced(model, prefixes[b], fed[:, b])
+        for got, ref in ((res["prefill"][b], last), (res["logits"][0, b], dec[0]), (res["logits"][1, b], dec[1])):
+            ok, err = helpers.tolerance_ok(got, ref, "bf16")
+            assert ok, (n_head, lens[b], err)
+
+
+@pytest.mark.parametrize("n_head,lens", [SHORT, WIDE])
+def test_full_attention_edges(n_head, lens):
+    import torch
+    from paper_2607_21042_amd import ftts
+    shape = workload.DitShape(n_layer=2, d_model=64 * n_head, n_head=n_head, d_head=64, d_ff=512, n_mel=64, d_cond=128)
+    w = workload.bf16_weights(workload.dit_master_weights(shape, seed=20))
+    lens = lens[:32]
+    dm, ora = ftts.DitDeviceModel(w, shape), odit.DiT(w, shape.n_head, shape.d_head, dtype=np.float32)
+    x, cond = workload.dit_inputs(shape, sum(lens), seed=41)
+    xg, cg = torch.from_numpy(x).cuda(), torch.from_numpy(cond).cuda().to(torch.bfloat16)
+    xo, vo = torch.empty_like(xg), torch.empty_like(xg)
+    ws = torch.empty(ftts.dit_workspace_bytes(dm.cfg, sum(lens)), dtype=torch.uint8, device="cuda")
+    print(f"full attention edges: {n_head} heads, {len(lens)} utterances", flush=True)
+    ftts.dit_step(dm, xg, cg, 0.4, 0.04, 1.5, xo, vo, ws, lens=lens)
+    torch.cuda.synchronize()
+    v, at = vo.cpu().numpy(), 0
+    for n in lens:
+        _, ref = ora.step(x[at:at + n], cond[at:at + n], 0.4, 0.04, 1.5)
+        ok, rel, err = helpers.dit_tolerance_ok(v[at:at + n], ref)
+        assert ok, (n_head, n, rel, err)
+        at += n
