@@ -317,15 +317,18 @@ __global__ __launch_bounds__(kAtWaves * 64, 3) void attn_tile_kernel(const AttnP
 // the chain load, product, softmax, product, merge.  Measured (us per layer), before
 // (32-key tiles, V transposed through registers) and now: 2 x 500 frames, 12 heads, no
 // mask, 12.7 and 10.5; 256 causal rows, 20 heads, 6.2 and 6.1.
+//
+// LAST: one workgroup per (sequence, head) that keeps only the last query, as row s of the
+// output: all that the layer feeding the logits needs.
 constexpr int kAsQ = 32;
-template <bool CAUSAL>
+template <bool CAUSAL, bool LAST>
 __global__ __launch_bounds__(kAtWaves * 64, 2) void attn_split_kernel(const AttnPrefillArgs a) {
     __shared__ __attribute__((aligned(1024))) char smem[kAtWaves * kAtStage];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int h = blockIdx.y, gt = blockIdx.x, sq = at_sequence(a, gt, lane);
+    const int h = blockIdx.y, gt = blockIdx.x, sq = LAST ? gt : at_sequence(a, gt, lane);
     const int row0 = a.seqs.cu[sq], len = a.seqs.cu[sq + 1] - row0;
     if (len <= 0) return;  // uniform over the workgroup
-    const int tile = gt - a.tiles_cu[sq];
+    const int tile = LAST ? (len - 1) / kAsQ : gt - a.tiles_cu[sq];
     const size_t ld = 3 * (size_t)a.d_model;
     const uint16_t* qkv = reinterpret_cast<const uint16_t*>(a.qkv);
     const int ql = lane & 31, hh = lane >> 5, qw = tile * kAsQ, qi = qw + ql;
@@ -418,7 +421,8 @@ __global__ __launch_bounds__(kAtWaves * 64, 2) void attn_split_kernel(const Attn
         }
     }
     const RowPair ls = swap32(st.l);
-    at_store(a, st, 1.0f / (ls.a + ls.b), smem + 3 * 34 * 64 * 4 + 1024, row0, 0, len, qw, h, lane);
+    at_store(a, st, 1.0f / (ls.a + ls.b), smem + 3 * 34 * 64 * 4 + 1024, LAST ? sq - (len - 1) : row0,
+             LAST ? len - 1 : 0, len, qw, h, lane);
 }
 
 int attn_tile_queries() { return kAtQ; }
@@ -433,8 +437,13 @@ hipError_t launch_attn_tile(bool causal, const AttnPrefillArgs& a, int tiles, hi
 
 hipError_t launch_attn_split(bool causal, const AttnPrefillArgs& a, int tiles, hipStream_t st) {
     const dim3 g(tiles, a.n_head), t(kAtWaves * 64);
-    if (causal) hipLaunchKernelGGL(attn_split_kernel<true>, g, t, 0, st, a);
-    else hipLaunchKernelGGL(attn_split_kernel<false>, g, t, 0, st, a);
+    if (causal) hipLaunchKernelGGL((attn_split_kernel<true, false>), g, t, 0, st, a);
+    else hipLaunchKernelGGL((attn_split_kernel<false, false>), g, t, 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_attn_last(const AttnPrefillArgs& a, hipStream_t st) {
+    hipLaunchKernelGGL((attn_split_kernel<true, true>), dim3(a.seqs.n, a.n_head), dim3(kAtWaves * 64), 0, st, a);
     return hipGetLastError();
 }
 

@@ -298,6 +298,8 @@ int attn_tile_queries();
 // The same in workgroups of attn_split_queries(), whose waves split the keys.
 hipError_t launch_attn_split(bool causal, const AttnPrefillArgs& a, int tiles, hipStream_t st);
 int attn_split_queries();
+// Causal attention of each sequence's last row only, to row s of the output (bf16).
+hipError_t launch_attn_last(const AttnPrefillArgs& a, hipStream_t st);
 hipError_t launch_gather_rows(const float* x, int d, const SeqTable& seqs, float* out, hipStream_t st);
 hipError_t launch_advance(int32_t* tokens, int32_t* positions, int32_t* seq_lens, int32_t* sampled,
                           int32_t* remaining, int32_t stop_token, bool retire_on_stop, int32_t* history,
