@@ -64,3 +64,26 @@ def test_full_attention_edges(n_head, lens):
         ok, rel, err = helpers.dit_tolerance_ok(v[at:at + n], ref)
         assert ok, (n_head, n, rel, err)
         at += n
+
+
+@pytest.mark.parametrize("mode", ["f32", "bf16", "w8a16", "w4a16"])
+@pytest.mark.parametrize("lens", [[1], [32, 33, 1, 200]])
+def test_prefill_without_logits_fills_the_same_cache(mode, lens):
+    """The last layer stops early without logits; the cached keys and values are the same bits."""
+    import torch
+    from paper_2607_21042_amd import ftts
+    shape = workload.ModelShape(n_layer=2, d_model=256, n_head=4, d_head=64, d_ff=512, vocab=640)
+    wd = {"f32": ftts.F32, "bf16": ftts.BF16, "w8a16": ftts.W8A16, "w4a16": ftts.W4A16}[mode]
+    dm = ftts.DeviceModel(workload.quantisable_weights(workload.master_weights(shape, seed=3)), shape, wd)
+    table, n_pages = helpers.make_block_table(lens)
+    pt = ftts.PageTableView(torch.from_numpy(table).cuda(), torch.zeros(len(lens), dtype=torch.int32, device="cuda"))
+    prefix = torch.from_numpy(workload.prefix_embeddings(lens, shape.d_model, seed=17)).cuda().to(ftts.act_dtype(wd))
+    pools = []
+    print(f"prefill without logits: {mode} {lens}", flush=True)
+    for logits in (None, torch.empty((len(lens), shape.vocab), device="cuda")):
+        kv = ftts.KVCache(shape, wd, n_pages)
+        ws = torch.empty(ftts.workspace_bytes(dm.cfg, len(lens), sum(lens)), dtype=torch.uint8, device="cuda")
+        ftts.prefill(dm, prefix, lens, pt, kv, logits, ws)
+        torch.cuda.synchronize()
+        pools.append(kv.pool)
+    assert pools[0].abs().max() > 0 and torch.equal(*pools)
