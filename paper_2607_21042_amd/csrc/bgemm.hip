@@ -26,6 +26,7 @@
 // step st from contiguous columns (bf16: k = h*16 + st*8 + i; W4A16: word
 // h*8+st), and the input operand uses the same map, so the dot product is
 // unchanged.
+#include "bgemm_stage.hpp"
 #include "gemm_epilogue.hpp"
 
 namespace ftts {
@@ -34,35 +35,22 @@ typedef __bf16 bgemm_bf16x8 __attribute__((ext_vector_type(8)));
 typedef float bgemm_f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bgemm_bf16x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kBgemmRows = 32;  // sequences per launch
-constexpr int kBgemmFeat = 32;  // features per MFMA tile (a workgroup owns FT tiles)
 constexpr int kBgemmMaxSplits = 12;  // K slices per feature tile (K <= 6144 for bf16 / W8A16)
 
 template <int WT> struct BChunk;  // one lane's share of one chunk
-template <> struct BChunk<FTTS_BF16> {
-    static constexpr int KC = 32, STEPS = 2, CB = 64;  // CB: bytes of one weight row per chunk
+template <> struct BChunk<FTTS_BF16> : BChunkShape<FTTS_BF16> {
     uint4 w[2];
     uint4 a[2];
 };
-template <> struct BChunk<FTTS_W8A16> {
-    static constexpr int KC = 32, STEPS = 2, CB = 32;
+template <> struct BChunk<FTTS_W8A16> : BChunkShape<FTTS_W8A16> {
     uint4 w[1];
     uint4 a[2];
 };
-template <> struct BChunk<FTTS_W4A16> {
-    static constexpr int KC = 128, STEPS = 8, CB = 64;
+template <> struct BChunk<FTTS_W4A16> : BChunkShape<FTTS_W4A16> {
     uint4 w[2];
     uint4 a[8];
     float s, z;
 };
-
-// Chunks per wave (its whole share of a K slice).  A LayerNorm input is staged as
-// fp32 rows in LDS (32 rows x 64 columns per wave, 128 for W4A16), which keeps
-// three workgroups per CU.
-constexpr int kBgemmWaves = 4, kBgemmThreads = kBgemmWaves * 64;
-template <int WT, bool LN> struct ChunksPerWave { static constexpr int value = LN ? 2 : 4; };
-template <> struct ChunksPerWave<FTTS_W4A16, false> { static constexpr int value = 2; };
-template <> struct ChunksPerWave<FTTS_W4A16, true> { static constexpr int value = 1; };
 
 // The LayerNorm input: 256 threads = 8 tile groups x 32 rows merge the tile
 // statistics; a slice's gains and biases sit in LDS.
@@ -92,48 +80,40 @@ __device__ __forceinline__ void load_chunk(const BgemmArgs& p, int n, int m, int
     }
 }
 
-// Weight staging.  A wave's chunks are consecutive, so each of its 32 rows is
-// one run of RB = CPW * CB bytes; direct-to-LDS loads bring the runs in with
-// 16 lanes (or fewer) per run and several whole runs per 1 KB instruction, and
-// the products read their operands from LDS.  The 16-byte pieces of row r are
-// stored XOR-swizzled by the row (row_swizzle) so that the 32 rows of one operand
-// read fall into different banks.  The loads go through a buffer descriptor: one
-// offset per lane and instruction, the slice's column as the scalar offset, and rows
-// past the matrix or the batch read as zero, instead of a clamped 64-bit address per
-// lane and load.
-// The 16 lanes whose 16-byte reads share a cycle take 256 bytes: rows of 64 and 128
-// bytes share that window four and two at a time.
-template <int PIECES>
-__device__ __forceinline__ int row_swizzle(int r) {
-    return PIECES == 4 ? (r >> 2) & 3 : PIECES == 8 ? (r >> 1) & 7 : r & (PIECES - 1);
-}
-template <int WT, bool LN, int FT> struct WStageShape {
-    static constexpr int RB = ChunksPerWave<WT, LN>::value * BChunk<WT>::CB;  // bytes per row
-    static constexpr int PIECES = RB / 16, BYTES = FT * kBgemmFeat * RB, OPS = BYTES / 1024;
-    static_assert(BYTES % 1024 == 0 && (PIECES & (PIECES - 1)) == 0, "staging shape");
-};
-
+// Staging (addresses in bgemm_stage.hpp): this wave's weight rows, or its 32 input
+// rows (fp32 under a LayerNorm, else bf16), over its run of chunks, by 1 KB
+// direct-to-LDS loads.  Rows past the matrix or the batch read as zero.
 template <int WT, bool LN, int FT>
 __device__ __forceinline__ void stage_weights(const BgemmArgs& p, int n0, int cw0, char* dst) {
-    using C = BChunk<WT>;
-    using SH = WStageShape<WT, LN, FT>;
-    constexpr int RPI = 1024 / SH::RB;  // rows per instruction
-    const int lane = threadIdx.x & 63;
-    const int row_bytes = WT == FTTS_W4A16 ? p.K / 2 : WT == FTTS_W8A16 ? p.K : p.K * 2;
+    using SH = WStage<WT, LN, FT>;
+    const int row_bytes = weight_row_bytes<WT>(p.K), bytes = weight_tile_bytes<WT, FT>(p.N, p.K, n0);
     const char* base = reinterpret_cast<const char*>(p.w) + (size_t)n0 * row_bytes;
-    const int bytes = min(p.N - n0, FT * kBgemmFeat) * row_bytes;
-    const int r0 = lane / SH::PIECES;  // row of the first instruction; instruction i adds RPI i
 #pragma unroll
-    for (int i = 0; i < SH::OPS; ++i) {
-        const int r = i * RPI + r0, pc = (lane % SH::PIECES) ^ row_swizzle<SH::PIECES>(r);  // the piece that lands in this lane's slot
-        buffer_to_lds16(base, bytes, dst + i * 1024, (uint32_t)(r * row_bytes + pc * 16), cw0 * C::CB);
-    }
+    for (int i = 0; i < SH::OPS; ++i)
+        buffer_to_lds16(base, bytes, dst + i * 1024,
+                        stage_offset<SH>(threadIdx.x & 63, i, row_bytes, cw0 * BChunk<WT>::CB), 0);
+}
+template <int WT>
+__device__ __forceinline__ void stage_x(const BgemmArgs& p, int cw0, char* dst) {
+    using SH = XStage<WT>;
+#pragma unroll
+    for (int i = 0; i < SH::OPS; ++i)
+        buffer_to_lds16(p.ln_x, p.B * p.K * 4, dst + i * 1024,
+                        stage_offset<SH>(threadIdx.x & 63, i, p.K * 4, cw0 * BChunk<WT>::KC * 4), 0);
+}
+template <int WT>
+__device__ __forceinline__ void stage_act(const BgemmArgs& p, int cw0, char* dst) {
+    using SH = AStage<WT>;
+#pragma unroll
+    for (int i = 0; i < SH::OPS; ++i)
+        buffer_to_lds16(p.act, p.B * p.K * 2, dst + i * 1024,
+                        stage_offset<SH>(threadIdx.x & 63, i, p.K * 2, cw0 * BChunk<WT>::KC * 2), 0);
 }
 
 // This lane's weight operands of local chunk j (row fr, k half h) from the staged rows.
 template <int WT, bool LN, int FT>
 __device__ __forceinline__ void read_weights(const char* src, int fr, int h, int j, BChunk<WT>& ch) {
-    using SH = WStageShape<WT, LN, FT>;
+    using SH = WStage<WT, LN, FT>;
     constexpr int NW = (int)(sizeof(ch.w) / 16), PPC = BChunk<WT>::CB / 16;
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
@@ -142,61 +122,20 @@ __device__ __forceinline__ void read_weights(const char* src, int fr, int h, int
     }
 }
 
-// LayerNorm input staging: this wave's 32 fp32 rows over its CPW chunks, RBX bytes
-// a row, by the same 1 KB direct-to-LDS loads and the same XOR swizzle of 16-byte
-// pieces.  Rows past the batch read as zero.
-template <int WT> struct XStageShape {
-    static constexpr int RBX = ChunksPerWave<WT, true>::value * BChunk<WT>::KC * 4;
-    static constexpr int PIECES = RBX / 16, BYTES = kBgemmRows * RBX, OPS = BYTES / 1024;
-    static_assert(BYTES % 1024 == 0 && (PIECES & (PIECES - 1)) == 0, "input staging shape");
-};
-
-template <int WT>
-__device__ __forceinline__ void stage_x(const BgemmArgs& p, int cw0, char* dst) {
-    using SH = XStageShape<WT>;
-    const int lane = threadIdx.x & 63, r0 = lane / SH::PIECES;
-    constexpr int RPI = 1024 / SH::RBX;
-#pragma unroll
-    for (int i = 0; i < SH::OPS; ++i) {
-        const int r = i * RPI + r0, pc = (lane % SH::PIECES) ^ row_swizzle<SH::PIECES>(r);  // columns pc*4 .. +3
-        buffer_to_lds16(p.ln_x, p.B * p.K * 4, dst + i * 1024, (uint32_t)(r * p.K * 4 + pc * 16), cw0 * BChunk<WT>::KC * 4);
-    }
-}
-
-// A 16-bit input is staged the same way: this wave's 32 bf16 rows over its CPW
-// chunks, RBA bytes a row.
-template <int WT> struct AStageShape {
-    static constexpr int RBA = ChunksPerWave<WT, false>::value * BChunk<WT>::KC * 2;
-    static constexpr int PIECES = RBA / 16, BYTES = kBgemmRows * RBA, OPS = BYTES / 1024;
-    static_assert(BYTES % 1024 == 0 && (PIECES & (PIECES - 1)) == 0, "input staging shape");
-};
-
-template <int WT>
-__device__ __forceinline__ void stage_act(const BgemmArgs& p, int cw0, char* dst) {
-    using SH = AStageShape<WT>;
-    const int lane = threadIdx.x & 63, r0 = lane / SH::PIECES;
-    constexpr int RPI = 1024 / SH::RBA;
-#pragma unroll
-    for (int i = 0; i < SH::OPS; ++i) {
-        const int r = i * RPI + r0, pc = (lane % SH::PIECES) ^ row_swizzle<SH::PIECES>(r);  // columns pc*8 .. +7
-        buffer_to_lds16(p.act, p.B * p.K * 2, dst + i * 1024, (uint32_t)(r * p.K * 2 + pc * 16), cw0 * BChunk<WT>::KC * 2);
-    }
-}
-
 // Eight consecutive bf16 inputs of row fr at column kl of this wave's staged run.
 template <int WT>
 __device__ __forceinline__ uint4 read_a8(const char* src, int fr, int kl) {
-    using SH = AStageShape<WT>;
+    using SH = AStage<WT>;
     const int q = (kl >> 3) ^ row_swizzle<SH::PIECES>(fr);
-    return *reinterpret_cast<const uint4*>(src + fr * SH::RBA + q * 16);
+    return *reinterpret_cast<const uint4*>(src + fr * SH::RB + q * 16);
 }
 
 // Four consecutive fp32 inputs of row fr at column kl of this wave's staged run.
 template <int WT>
 __device__ __forceinline__ float4 read_x4(const char* src, int fr, int kl) {
-    using SH = XStageShape<WT>;
+    using SH = XStage<WT>;
     const int q = (kl >> 2) ^ row_swizzle<SH::PIECES>(fr);
-    return *reinterpret_cast<const float4*>(src + fr * SH::RBX + q * 16);
+    return *reinterpret_cast<const float4*>(src + fr * SH::RB + q * 16);
 }
 
 // The weight operand of MFMA step st (8 bf16; quantised codes expanded exactly).
@@ -242,21 +181,21 @@ __global__ __launch_bounds__(kBgemmThreads) void bgemm_kernel(const BgemmArgs p)
     constexpr int SLICE = CPW * kBgemmWaves * C::KC, GBPER = (SLICE + NT - 1) / NT;  // columns of a K slice
     // staged input rows (fp32 for a LayerNorm input, else bf16); once consumed, the
     // wave's buffer takes its partial tile for the sum over waves
-    constexpr int IN_BYTES = LN ? XStageShape<WT>::BYTES : AStageShape<WT>::BYTES;
+    constexpr int IN_BYTES = LN ? XStage<WT>::BYTES : AStage<WT>::BYTES;
     static_assert(IN_BYTES >= kBgemmRows * FEAT * 4, "wave tile must fit the staged inputs");
     __shared__ __attribute__((aligned(1024))) char s_xs[kBgemmWaves][IN_BYTES];
     __shared__ __attribute__((aligned(16))) float s_g[LN ? SLICE : 1];
     __shared__ __attribute__((aligned(16))) float s_b[LN ? SLICE : 1];
     __shared__ float2 s_gs[LN ? kLnGroups : 1][LN ? kBgemmRows : 1];
     __shared__ float s_mean[LN ? kBgemmRows : 1], s_rstd[LN ? kBgemmRows : 1];
-    __shared__ __attribute__((aligned(1024))) char s_wt[kBgemmWaves][WStageShape<WT, LN, FT>::BYTES];
+    __shared__ __attribute__((aligned(1024))) char s_wt[kBgemmWaves][WStage<WT, LN, FT>::BYTES];
     int& s_last = *reinterpret_cast<int*>(s_wt[0]);  // used only after every product is formed
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int f = blockIdx.x, s = blockIdx.y, S = gridDim.y;
     const int n0 = f * FEAT;
     const int fr = lane & 31, h = lane >> 5;
     const int nchunks = p.K / C::KC;
-    const int c0 = s * nchunks / S, c1 = (s + 1) * nchunks / S;
+    const int c0 = bgemm_slice(s, S, nchunks), c1 = bgemm_slice(s + 1, S, nchunks);
     // this thread's epilogue elements: feature ne, rows mrow(i)
     const int ne = min(n0 + (tid & (FEAT - 1)), p.N - 1);
     auto mrow = [&](int i) { return tid / FEAT + (NT / FEAT) * i; };
@@ -295,9 +234,9 @@ __global__ __launch_bounds__(kBgemmThreads) void bgemm_kernel(const BgemmArgs p)
             pre.slot[i] = p.kv.seq_lens[m];
         }
     }
-    // 3. every weight and input load of this wave: its chunks are c0 + wave * CPW + j
+    // 3. every weight and input load of this wave: its chunks are cw0 + j
     // (chunks past the slice hold other columns, or zero, and are not used)
-    const int cw0 = c0 + wave * CPW;
+    const int cw0 = bgemm_wave_chunk<WT, LN>(c0, wave);
     stage_weights<WT, LN, FT>(p, n0, cw0, s_wt[wave]);
     if constexpr (LN) stage_x<WT>(p, cw0, s_xs[wave]);
     else stage_act<WT>(p, cw0, s_xs[wave]);
