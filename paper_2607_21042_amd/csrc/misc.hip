@@ -2,6 +2,7 @@
 // per-row activity flag every later kernel reads), LayerNorm over packed rows
 // (prefill), row gathers, the next-token sampler and the weight quantiser.
 #include <algorithm>
+#include <cfloat>
 #include <climits>
 
 #include "ftts_internal.hpp"
@@ -290,12 +291,16 @@ hipError_t launch_assemble_prefix(int wdtype, const AssembleArgs& a, int rows, h
 //
 // Top-k without k sequential block reductions.  If t is the k-th largest of the 256
 // maxima over groups of four lanes, at least k entries are >= t, so every one of the k
-// best is, and few others are (about 32 in all for k = 30, whatever the row's length).
-// t is found by counting, one thread per group maximum; the entries >= t are
+// best is, and few others are (about 32 in all for k = 30 and spread-out logits).
+// t is found by counting, one thread per group maximum; the finite entries >= t are
 // collected in LDS as 64-bit keys that sort by (value, index), each is ranked by
-// counting the keys above it, and ranks below k fill the ordered top-k list.  Rows
-// with more than kSampCand candidates (massive exact ties) take k rounds of block
-// argmax instead.
+// counting the keys above it, and ranks below k fill the ordered top-k list.  Where
+// fewer than k groups hold an entry above -inf (a row of fewer than 4 k entries, or one
+// masked to a short run), t is -inf and every entry above -inf is collected; if these are fewer
+// than k, the lowest-index -inf entries take the ranks after them (32 rows, k = 30: 100
+// entries 9.6 us, 8194 masked to a run of 90 10.4 us; by rounds of argmax 50 and 57).  Rows with more than
+// kSampCand candidates (massive exact ties, or more entries than that in fewer than k
+// groups) take k rounds of block argmax instead.
 //
 // A row is 33 KB, so the kernel is bound by its chain of short steps: with 256 threads
 // (64 entries each, 33 divisions of them in use, a per-wave threshold that let about
@@ -430,7 +435,7 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
         if (gt < top_k && top_k <= ge) s_t = own;  // (every thread that writes holds the same value)
     }
     __syncthreads();
-    const float t = s_t;
+    const float t = fmaxf(s_t, -FLT_MAX);  // (neither the slots past the row nor masked entries compete)
     if (lm >= t) {
 #pragma unroll
         for (int j = 0; j < kSampPer; ++j)
@@ -445,6 +450,14 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
     const int total = s_cnt;
     if (total <= kSampCand) {
         if (tid < 8) s_key[total + tid] = 0;  // below every key, so that the ranking reads whole groups of 8
+        if (total < top_k && wave == 0) {  // at least k - total of the first k <= 64 entries are -inf
+            const uint64_t none = __ballot(lane < top_k && z[0] == -INFINITY);
+            const int r = total + __popcll(none & ((1ull << lane) - 1));
+            if (((none >> lane) & 1) && r < top_k) {
+                selv[r] = -INFINITY;
+                seli[r] = lane;
+            }
+        }
         __syncthreads();
         for (int c = tid; c < total; c += kSampThreads) {
             const uint64_t own = s_key[c];

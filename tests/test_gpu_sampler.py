@@ -43,3 +43,65 @@ def test_sampler_edges(V):
         for b in range(B):
             want, det = osample.sample(ref[b], T, k, p, u[b])
             assert got[b] == want or osample.near_boundary(det), (T, k, p, b, got[b], want)
+
+
+@pytest.mark.parametrize("V", [64, 100, 200, 1025, 8194])
+def test_sampler_few_finite_entries(V):
+    """Rows with 0 .. k + 2 finite entries, in one run or scattered, the rest -inf
+    (and a few led by +inf, whose exponentials are NaN): the ranks past the finite
+    entries go to the lowest-index -inf ones."""
+    import torch
+    from paper_2607_21042_amd import ftts
+    rng = np.random.default_rng(V)
+    for T, k, p in [(0.8, 2, 0.9), (0.8, 30, 0.8), (1.7, 64, 1.0)]:
+        n_finite = [n for n in (0, 1, 2, 3, k // 2, k - 1, k, k + 1, k + 2) if n <= V]
+        z = np.full((3 * len(n_finite), V), -np.inf, np.float32)
+        for i, n in enumerate(n_finite):
+            at = int(rng.integers(0, V - n + 1))
+            z[3 * i, at:at + n] = rng.standard_normal(n)
+            z[3 * i + 1, rng.permutation(V)[:n]] = rng.standard_normal(n)
+            z[3 * i + 2, V - n:] = rng.standard_normal(n)
+            z[3 * i + 2, V // 2] = np.inf
+        B = z.shape[0]
+        u = workload.uniforms(1, B, seed=V + k)[0]
+        out = torch.empty(B, dtype=torch.int32, device="cuda")
+        print(f"sampler with few finite entries: V={V} k={k}", flush=True)
+        ftts.sample(torch.from_numpy(z).cuda(), ftts.Sampling(T, k, p), torch.from_numpy(u).cuda(), out)
+        got = out.cpu().numpy()
+        for b in range(B):
+            with np.errstate(invalid="ignore"):
+                want, det = osample.sample(z[b], T, k, p, u[b])
+            assert got[b] == want or osample.near_boundary(det), (T, k, p, b, got[b], want)
+
+
+def test_short_and_masked_rows_take_the_fast_path():
+    """A row of fewer than 4 k entries, or masked to a short run, costs no more than a
+    full row of 8194: the ranked list serves both (k rounds of block argmax, which only
+    a crowd of exact ties takes, would be several times slower).  The bar of 1.5 leaves
+    room for timing noise: these rows read less and rank about as many entries."""
+    import torch
+    from paper_2607_21042_amd import ftts
+    B, k = 32, 30
+    u = torch.from_numpy(workload.uniforms(1, B, seed=9)[0]).cuda()
+    out = torch.empty(B, dtype=torch.int32, device="cuda")
+    full = torch.from_numpy(workload.random_logits(B, 8194, seed=5)).cuda()
+    masked = torch.full_like(full, float("-inf"))
+    masked[:, 4000:4090] = full[:, 4000:4090]
+    short = full[:, :100].contiguous()
+
+    def us(z):
+        best = 1e9
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(100):
+                ftts.sample(z, ftts.Sampling(0.8, k, 0.8), u, out)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 10)
+        return best
+
+    us(full)
+    t = {name: us(z) for name, z in (("full", full), ("short", short), ("masked", masked))}
+    print(f"sampler us per call: {t}", flush=True)
+    assert t["short"] <= 1.5 * t["full"] and t["masked"] <= 1.5 * t["full"], t
