@@ -134,11 +134,16 @@ __device__ __forceinline__ void at_softmax(AtState& a, at_f32x16 (&s)[2], int k0
     for (int j = 0; j < 16; ++j)
         a.l = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pw[j]), ones, a.l, false);
 }
-// O^T += V^T P^T.  v[d][e][st]: keys 16 st + 8 e + hh*4 + 0..3 of dim 32 d + lane % 32;
-// k slots hh*8 .. +7 of step st carry the same keys on both operands.
-__device__ __forceinline__ void at_pv(AtState& a, const uint64_t (&v)[2][2][4], const uint32_t (&pw)[16]) {
+// O^T += V^T P^T over the tile's keys k0 .. k0 + 63.  v[d][e][st]: keys 16 st + 8 e +
+// hh*4 + 0..3 of dim 32 d + lane % 32; k slots hh*8 .. +7 of step st carry the same keys
+// on both operands.  CAUSAL: the second half is left out where no query qw .. qw + 31
+// of the wave sees it, so that a later row that is not finite (0 x NaN is NaN) stays
+// out of every earlier block of 32.
+template <bool CAUSAL>
+__device__ __forceinline__ void at_pv(AtState& a, const uint64_t (&v)[2][2][4], const uint32_t (&pw)[16], int k0, int qw) {
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
+        if (CAUSAL && st == 2 && k0 >= qw) return;  // (uniform over the wave)
         const at_bf16x8 pb = at_op(make_uint4(pw[4 * st], pw[4 * st + 1], pw[4 * st + 2], pw[4 * st + 3]));
         auto vop = [&](int d) {
             return at_op(make_uint4((uint32_t)v[d][0][st], (uint32_t)(v[d][0][st] >> 32), (uint32_t)v[d][1][st],
@@ -300,7 +305,7 @@ __global__ __launch_bounds__(kAtWaves * 64, 3) void attn_tile_kernel(const AttnP
         at_softmax<CAUSAL>(st, s, k0, len, qw, qi, hh, pw);
         at_wait_lds();
         at_tie_v(v);
-        at_pv(st, v, pw);
+        at_pv<CAUSAL>(st, v, pw, k0, qw);
     }
     __syncthreads();  // the stages are free: rows go out through 4 KB per wave
     if (qw >= len) return;
@@ -382,7 +387,7 @@ __global__ __launch_bounds__(kAtWaves * 64, 2) void attn_split_kernel(const Attn
         __builtin_amdgcn_sched_barrier(0);
         if (more) load(t + kAtWaves, 1);
         __builtin_amdgcn_sched_barrier(0);
-        at_pv(st, v, pw);
+        at_pv<CAUSAL>(st, v, pw, t * kAtK, qw);
     }
     __syncthreads();  // every wave has read its stage: the partials of waves 1 .. 3 go there, lane for lane
     float* mrg = reinterpret_cast<float*>(smem);  // [3][34][64]

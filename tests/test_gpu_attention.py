@@ -87,3 +87,41 @@ def test_prefill_without_logits_fills_the_same_cache(mode, lens):
         torch.cuda.synchronize()
         pools.append(kv.pool)
     assert pools[0].abs().max() > 0 and torch.equal(*pools)
+
+
+@pytest.mark.parametrize("n_head,seqs", [(4, 2), (8, 24)])
+def test_non_finite_rows_stay_causal(n_head, seqs):
+    """A NaN row of a prefix reaches later rows only, and the 32-row block that it is
+    in (its masked probability is 0, and 0 x NaN is NaN inside one matrix product):
+    the keys and values of every earlier block keep their bits, on the short grid and
+    on the wide one, and so do the other sequences'."""
+    import torch
+    from paper_2607_21042_amd import ftts
+    shape = workload.ModelShape(n_layer=3, d_model=64 * n_head, n_head=n_head, d_head=64, d_ff=512, vocab=640)
+    dm = ftts.DeviceModel(workload.bf16_weights(workload.master_weights(shape, seed=3)), shape, ftts.BF16)
+    lens = [230] * seqs
+    assert (seqs * 2 * n_head >= 256) == (n_head == 8)
+    table, n_pages = helpers.make_block_table(lens)
+    pt = ftts.PageTableView(torch.from_numpy(table).cuda(), torch.zeros(seqs, dtype=torch.int32, device="cuda"))
+    clean = torch.from_numpy(workload.prefix_embeddings(lens, shape.d_model, seed=17)).cuda().to(torch.bfloat16)
+
+    def cache(prefix):
+        kv = ftts.KVCache(shape, ftts.BF16, n_pages)
+        ws = torch.empty(ftts.workspace_bytes(dm.cfg, seqs, sum(lens)), dtype=torch.uint8, device="cuda")
+        ftts.prefill(dm, prefix, lens, pt, kv, None, ws)
+        torch.cuda.synchronize()
+        # [layer][seq][k|v][head][row][dim]
+        pool = kv.pool[:, torch.from_numpy(table).cuda().long()]
+        return pool.permute(0, 1, 3, 4, 2, 5, 6).flatten(4, 5)[..., :lens[0], :].float()
+
+    ref = cache(clean)
+    assert torch.isfinite(ref).all()
+    for bad in (45, 100, 190, 229):
+        x = clean.clone()
+        x[bad] = float("nan")  # a row of sequence 0
+        print(f"non-finite row {bad}: {n_head} heads, {seqs} prefixes", flush=True)
+        got = cache(x)
+        assert torch.isnan(got[0, 0, :, :, bad]).all()
+        rows = bad // 32 * 32
+        others, earlier = torch.equal(got[:, 1:], ref[:, 1:]), torch.equal(got[:, 0, :, :, :rows], ref[:, 0, :, :, :rows])
+        assert others and earlier, (bad, others, earlier)
