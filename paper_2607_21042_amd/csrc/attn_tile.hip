@@ -353,8 +353,9 @@ __global__ __launch_bounds__(kAtWaves * 64, 2) void attn_split_kernel(const Attn
     };
     uint4 qr[4];
     at_load_q(qkv + (size_t)(row0 + min(qi, len - 1)) * ld + h * kHeadDim, hh, qr);
-    if (wave < nt) {
+    if (wave < nt) {  // (the counted wait for K relies on this order)
         load(wave, 0);
+        __builtin_amdgcn_sched_barrier(0);
         load(wave, 1);
     }
     const AtAddr ad = at_addresses(lds_address(own), lane);

@@ -74,7 +74,10 @@ __device__ __forceinline__ void lg_read4(const uint32_t (&addr)[4], lg_bf16x8 (&
 #pragma unroll
     for (int k = 0; k < 4; ++k) o[k] = lg_read<OFF>(addr[k]);
 }
-__device__ __forceinline__ void lg_wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void lg_wait_lds() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
 // Keeps the uses of o behind the wait that precedes this call.
 template <int N>
 __device__ __forceinline__ void lg_tie(lg_bf16x8 (&o)[N][4]) {

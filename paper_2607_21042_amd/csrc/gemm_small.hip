@@ -62,7 +62,10 @@ __device__ __forceinline__ uint4 sg_read(uint32_t addr) {
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFF) : "memory");
     return __builtin_bit_cast(uint4, r);
 }
-__device__ __forceinline__ void sg_wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void sg_wait_lds() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
 template <int N>
 __device__ __forceinline__ void sg_tie(uint4 (&o)[N]) {
 #pragma unroll
@@ -184,8 +187,10 @@ __global__ __launch_bounds__(kSgThreads, 2) void gemm_small_kernel(const GemmArg
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[n][i] = 0.f;
 #pragma unroll
-    for (int s = 0; s < S - 1; ++s)
+    for (int s = 0; s < S - 1; ++s) {  // (the counted waits rely on this order)
         if (s < nk) load(s, s);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     int st = 0;
     for (int kt = 0; kt < nk; ++kt) {
         sg_wait_stage<NI>(min(S - 2, nk - 1 - kt));
