@@ -425,6 +425,21 @@ int ftts_dit_step(const ftts_dit_weights* w, const float* x, const void* cond, c
                   float t, float dt, float cfg_w, float* x_out, float* v_out, void* ws, size_t ws_bytes,
                   void* stream);
 
+/* ---- launch shapes ----------------------------------------------------------------- */
+/* How the prefill (and, in bf16, the DiT step) runs a linear of M rows, N outputs and K
+ * inputs on the matrix cores.  Host only: a pure function of its arguments that touches
+ * no device.  wdtype FTTS_BF16, FTTS_W8A16 or FTTS_W4A16 (FTTS_E_DTYPE otherwise); N a
+ * multiple of 8, K of 64 (quantised: of 128), 1 <= M <= 2^24 (FTTS_E_SHAPE otherwise). */
+typedef struct {
+    int32_t rows_large;            /* rows 0 .. rows_large - 1 run in tiles of */
+    int32_t large_rows, large_cols;/*   this size (0 if rows_large is 0) */
+    int32_t small_cols;            /* the rest in tiles of 64 rows and this many columns, */
+    int32_t splits;                /*   K in this many slices (both 0 if there is no rest) */
+    int32_t scratch_counters;      /* split-K scratch a workspace holds for the linear */
+    int64_t scratch_floats;        /*   at any row count up to M */
+} ftts_linear_shape;
+int ftts_linear_plan(int32_t wdtype, int32_t M, int32_t N, int32_t K, ftts_linear_shape* out);
+
 #ifdef __cplusplus
 }
 #endif

@@ -153,6 +153,7 @@ struct PrefillWs {
     int32_t* active; // [B] all ones (head GEMV reads no flags; kept for symmetry)
     float* part;     // split-K partial tiles of the GEMMs (16-bit modes, short prefixes)
     uint32_t* count; // their per-tile arrival counters
+    GemmScratch split;  // the sizes of part and count
     int32_t* slots;  // [M] KV slot of every row
 };
 
@@ -226,6 +227,18 @@ size_t decode_bytes(const ftts_config& c, int B, DecodeWs* out, char* base) {
     return off;
 }
 
+// The split-K scratch that serves each of a model's linears in turn.
+template <int L>
+GemmScratch widest_scratch(int wdtype, int M, const int (&NK)[L][2]) {
+    GemmScratch r{0, 0};
+    for (const auto& t : NK) {
+        const GemmScratch s = gemm_scratch(wdtype, M, t[0], t[1]);
+        r.part_floats = std::max(r.part_floats, s.part_floats);
+        r.n_count = std::max(r.n_count, s.n_count);
+    }
+    return r;
+}
+
 size_t prefill_bytes(const ftts_config& c, int B, int M, PrefillWs* out, char* base) {
     const size_t e = act_bytes(c);
     size_t off = mega_bytes(nullptr, nullptr);
@@ -236,14 +249,14 @@ size_t prefill_bytes(const ftts_config& c, int B, int M, PrefillWs* out, char* b
     char* h = take((size_t)M * c.d_ff * e);
     char* xl = take((size_t)B * c.d_model * 4);
     char* act = take((size_t)B * 4);
-    // split-K scratch for any row count (a smaller call may split where a larger one does not)
-    const bool mfma = c.wdtype != FTTS_F32 && M > 0;
-    char* part = mfma ? take(kGemmPartFloats * 4) : nullptr;
-    char* count = mfma ? take(kGemmSplitTiles * 4) : nullptr;
+    const int NK[4][2] = {{3 * c.d_model, c.d_model}, {c.d_model, c.d_model}, {c.d_ff, c.d_model}, {c.d_model, c.d_ff}};
+    const GemmScratch split = widest_scratch(c.wdtype, M, NK);
+    char* part = split.n_count ? take(split.part_floats * 4) : nullptr;
+    char* count = split.n_count ? take((size_t)split.n_count * 4) : nullptr;
     char* slots = take((size_t)M * 4);
     if (out)
         *out = PrefillWs{(float*)x,   a,     qkv, h, (float*)xl, (int32_t*)act, (float*)part, (uint32_t*)count,
-                         (int32_t*)slots};
+                         split,       (int32_t*)slots};
     return off;
 }
 
@@ -676,12 +689,11 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
         seqs.cu[b + 1] = (int)M;
         ap.tiles_cu[b + 1] = ap.tiles_cu[b] + (lens[b] + prefill_tile_rows(c.wdtype) - 1) / prefill_tile_rows(c.wdtype);
     }
-    const size_t need = prefill_bytes(c, B, (int)M, nullptr, nullptr);
+    PrefillWs P;
+    const size_t need = prefill_bytes(c, B, (int)M, &P, reinterpret_cast<char*>(ws));
     if (ws_bytes < need) return fail(FTTS_E_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, need);
 
     hipStream_t st = (hipStream_t)stream;
-    PrefillWs P;
-    prefill_bytes(c, B, (int)M, &P, reinterpret_cast<char*>(ws));
     const int d = c.d_model, F = c.d_ff, V = c.vocab, Mi = (int)M;
 
     (void)hipGetLastError();
@@ -705,7 +717,7 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
         if ((e = launch_assemble_prefix(c.wdtype, as, Mi, st)) != hipSuccess) return hip_fail(e, "input assembly");
     }
     if ((e = launch_prefill_setup(seqs, pt->block_table, pt->max_pages, kv->n_pages, Mi, P.slots, P.count,
-                                  P.count ? kGemmSplitTiles : 0, st)) !=
+                                  P.split.n_count, st)) !=
         hipSuccess)
         return hip_fail(e, "prefill setup");
 
@@ -740,6 +752,8 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
         GemmArgs g{};
         g.part = P.part;
         g.count = P.count;
+        g.part_floats = P.split.part_floats;
+        g.n_count = P.split.n_count;
         g.a = P.a;
         g.w = L.qkv.w;
         g.scale = (const uint16_t*)L.qkv.scale;
@@ -873,7 +887,7 @@ struct DitWs {
     float* e;        // [D] time embedding
     float* part;     // split-K partial tiles
     uint32_t* count; // split-K arrival counters
-    size_t n_count;
+    GemmScratch split;  // the sizes of part and count
 };
 
 int check_dit_config(const ftts_dit_config* c) {
@@ -903,11 +917,13 @@ size_t dit_bytes(const ftts_dit_config& c, int T, DitWs* out, char* base) {
     char* vel = take(M * (size_t)c.n_mel * 4);
     char* u = take(d * 4);
     char* e = take(d * 4);
-    char* part = take(kGemmPartFloats * 4);
-    char* count = take(kGemmSplitTiles * 4);
+    const int D = c.d_model, F = c.d_ff;
+    const int NK[6][2] = {{D, (int)Kin}, {3 * D, D}, {D, D}, {F, D}, {D, F}, {c.n_mel, D}};
+    const GemmScratch split = widest_scratch(FTTS_BF16, (int)M, NK);
+    char* part = split.n_count ? take(split.part_floats * 4) : nullptr;
+    char* count = split.n_count ? take((size_t)split.n_count * 4) : nullptr;
     if (out)
-        *out = DitWs{(float*)h, a, qkv, f, (float*)vel, (float*)u, (float*)e, (float*)part, (uint32_t*)count,
-                     kGemmSplitTiles};
+        *out = DitWs{(float*)h, a, qkv, f, (float*)vel, (float*)u, (float*)e, (float*)part, (uint32_t*)count, split};
     return off;
 }
 
@@ -955,6 +971,8 @@ GemmArgs dit_gemm(const ftts_linear& l, const void* a, int M, int N, int K, void
     g.out = out;
     g.part = W.part;
     g.count = W.count;
+    g.part_floats = W.split.part_floats;
+    g.n_count = W.split.n_count;
     return g;
 }
 
@@ -988,12 +1006,11 @@ int ftts_dit_step(const ftts_dit_weights* w, const float* x, const void* cond, c
     if (c.d_cond > 0) TRY(check_ptr(cond, "cond"));
     if (v_out) TRY(check_ptr(v_out, "v_out"));
     TRY(check_ptr(ws, "workspace"));
-    const size_t need = dit_bytes(c, T, nullptr, nullptr);
+    DitWs W;
+    const size_t need = dit_bytes(c, T, &W, reinterpret_cast<char*>(ws));
     if (ws_bytes < need) return fail(FTTS_E_WORKSPACE, "workspace too small: %zu < %zu", ws_bytes, need);
 
     hipStream_t st = (hipStream_t)stream;
-    DitWs W;
-    dit_bytes(c, T, &W, reinterpret_cast<char*>(ws));
     const int d = c.d_model, F = c.d_ff, M = 2 * T, Kin = c.n_mel + c.d_cond;
 
     (void)hipGetLastError();
@@ -1012,7 +1029,7 @@ int ftts_dit_step(const ftts_dit_weights* w, const float* x, const void* cond, c
     pa.h = W.h;
     pa.vel = W.vel;
     pa.count = W.count;
-    pa.n_count = W.n_count;
+    pa.n_count = W.split.n_count;
     if ((e = launch_dit_prepare(pa, st)) != hipSuccess) return hip_fail(e, "step inputs");
     // h = [x | c] W_in^T + b_in + e(t)
     if ((e = launch_gemm(FTTS_BF16, EPI_RESID, dit_gemm(w->in, W.a, M, d, Kin, W.h, W),

@@ -236,6 +236,8 @@ struct GemmArgs {
     SeqTable seqs;
     float* part;             // split K: [S] fp32 partial tiles of whole 64 x bn blocks
     uint32_t* count;         // split K: per-tile arrival counters, zero between calls
+    size_t part_floats;      // how much of each there is
+    int n_count;
 };
 struct GemmPlan {      // 16-bit-mode GEMM launch shape
     int rows_large;    // rows 0 .. rows_large - 1 take gemm_large_kernel (0: none) in tiles of
@@ -243,9 +245,10 @@ struct GemmPlan {      // 16-bit-mode GEMM launch shape
     int bn, splits;    // the rest take gemm_small_kernel: tiles of 64 rows and bn columns, K in `splits` slices
 };
 GemmPlan gemm_plan(int wdtype, int M, int N, int K);
-// A plan that splits K has at most this many tiles, and workgroups (tiles x slices).
-constexpr int kGemmSplitTiles = 256, kGemmSplitGroups = 512;
-constexpr size_t kGemmPartFloats = (size_t)kGemmSplitGroups * 64 * 128;  // GemmArgs::part (GemmArgs::count: kGemmSplitTiles)
+// Split-K scratch (GemmArgs::part, GemmArgs::count) that covers every plan of an (N, K)
+// linear at up to M rows; nothing where no such plan splits.
+struct GemmScratch { size_t part_floats; int n_count; };
+GemmScratch gemm_scratch(int wdtype, int M, int N, int K);
 
 struct AttnPrefillArgs {
     const void* qkv;         // [M][3d] activation dtype

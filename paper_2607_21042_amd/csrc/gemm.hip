@@ -5,6 +5,7 @@
 // thread).
 #include <algorithm>
 
+#include "decode_entry.hpp"
 #include "gemm_epilogue.hpp"
 
 namespace ftts {
@@ -124,14 +125,17 @@ static double small_us(int wdtype, int bn, int splits, int M, int N, int K) {
     return p[0] + (K / 64) / (double)splits * std::max(p[1], p[2] * load) + (splits > 1 ? p[3] : 0.0);
 }
 
+// A plan that splits K has at most this many tiles, and workgroups (tiles x slices), of
+// at least 6 steps of 64 columns each, as far as was timed.
+constexpr int kSplitTiles = 256, kSplitGroups = 512, kMaxSplits = 8, kSplitSteps = 6;
+
 // The best small plan for M rows (its modelled time in *us).
 static void plan_small(int wdtype, int M, int N, int K, GemmPlan* p, double* us) {
     *us = 1e30;
     for (int bn = 64; bn <= 128; bn += 64) {
         const long tiles = (long)((M + 63) / 64) * ((N + bn - 1) / bn);
-        for (int s = 1; s <= 8; ++s) {
-            // (a slice keeps at least 6 steps of 64 columns, as far as was timed)
-            if (s > 1 && (tiles > kGemmSplitTiles || tiles * s > kGemmSplitGroups || K / 64 / s < 6)) break;
+        for (int s = 1; s <= kMaxSplits; ++s) {
+            if (s > 1 && (tiles > kSplitTiles || tiles * s > kSplitGroups || K / 64 / s < kSplitSteps)) break;
             const double t = small_us(wdtype, bn, s, M, N, K);
             if (t < *us) *us = t, p->bn = bn, p->splits = s;
         }
@@ -165,6 +169,26 @@ GemmPlan gemm_plan(int wdtype, int M, int N, int K) {
     return best;
 }
 
+// (A call of fewer rows may split where one of M rows does not, and the rows past the
+// large kernel's are planned by themselves: the most that the small plan of any row
+// count up to M writes.  A plan depends on the count of 64-row blocks only, and splits
+// while there are at most kSplitTiles tiles.)
+GemmScratch gemm_scratch(int wdtype, int M, int N, int K) {
+    GemmScratch r{0, 0};
+    if (wdtype == FTTS_F32 || K / 64 / kSplitSteps < 2) return r;
+    const int blocks = std::min((M + 63) / 64, kSplitTiles / ((N + 127) / 128));
+    for (int b = 1; b <= blocks; ++b) {
+        GemmPlan p{};
+        double us;
+        plan_small(wdtype, 64 * b, N, K, &p, &us);
+        if (p.splits < 2) continue;
+        const int tiles = b * ((N + p.bn - 1) / p.bn);
+        r.part_floats = std::max(r.part_floats, (size_t)tiles * p.splits * 64 * p.bn);
+        r.n_count = std::max(r.n_count, tiles);
+    }
+    return r;
+}
+
 hipError_t launch_gemm(int wdtype, int epi, const GemmArgs& a, const GemmPlan& p, hipStream_t st) {
     if (wdtype == FTTS_F32) {
         const dim3 g((a.N + 63) / 64, (a.M + 63) / 64);
@@ -192,3 +216,17 @@ hipError_t launch_gemm(int wdtype, int epi, const GemmArgs& a, const GemmPlan& p
 }
 
 }  // namespace ftts
+
+extern "C" int ftts_linear_plan(int32_t wdtype, int32_t M, int32_t N, int32_t K, ftts_linear_shape* out) {
+    if (!out) return ftts::set_error(FTTS_E_INVALID_ARG, "out is NULL");
+    if (wdtype < FTTS_BF16 || wdtype > FTTS_W4A16)
+        return ftts::set_error(FTTS_E_DTYPE, "no matrix-core linears in wdtype %d", wdtype);
+    if (M < 1 || M > (1 << 24) || N < 8 || N % 8 || K < 64 || K % (wdtype == FTTS_BF16 ? 64 : 128))
+        return ftts::set_error(FTTS_E_SHAPE, "no matrix-core linear of %d x %d x %d", M, N, K);
+    const ftts::GemmPlan p = ftts::gemm_plan(wdtype, M, N, K);
+    const ftts::GemmScratch s = ftts::gemm_scratch(wdtype, M, N, K);
+    *out = ftts_linear_shape{p.rows_large, p.rows_large ? 64 * p.mt : 0, p.rows_large ? 128 * p.nt : 0,
+                             p.rows_large < M ? p.bn : 0, p.rows_large < M ? p.splits : 0, s.n_count,
+                             (int64_t)s.part_floats};
+    return FTTS_OK;
+}

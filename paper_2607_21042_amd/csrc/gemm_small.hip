@@ -402,7 +402,11 @@ static hipError_t small_by_epi(int epi, const GemmArgs& a, int bn, int splits, h
 
 hipError_t launch_gemm_small(int wdtype, int epi, const GemmArgs& a, int bn, int splits, hipStream_t st) {
     if (a.K % (wdtype == FTTS_BF16 ? 64 : 128) || a.N % 8) return hipErrorInvalidValue;
-    if (splits > 1 && (!a.part || !a.count)) return hipErrorInvalidValue;
+    if (splits > 1) {
+        const size_t tiles = (size_t)((a.M + kSgM - 1) / kSgM) * ((a.N + bn - 1) / bn);
+        if (!a.part || !a.count || tiles > (size_t)a.n_count || tiles * splits * kSgM * bn > a.part_floats)
+            return hipErrorInvalidValue;
+    }
     switch (wdtype) {
         case FTTS_BF16: return small_by_epi<FTTS_BF16>(epi, a, bn, splits, st);
         case FTTS_W8A16: return small_by_epi<FTTS_W8A16>(epi, a, bn, splits, st);

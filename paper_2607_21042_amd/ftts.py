@@ -77,6 +77,11 @@ class Sampling(_c.Structure):
     _fields_ = [("temperature", f32), ("top_k", i32), ("top_p", f32)]
 
 
+class LinearShape(_c.Structure):
+    _fields_ = [("rows_large", i32), ("large_rows", i32), ("large_cols", i32), ("small_cols", i32), ("splits", i32),
+                ("scratch_counters", i32), ("scratch_floats", _c.c_int64)]
+
+
 _lib = None
 
 
@@ -123,6 +128,8 @@ def lib():
         L.ftts_dit_step.restype = _c.c_int
         L.ftts_dit_step.argtypes = [P(DitWeights), vp, vp, P(i32), i32, f32, f32, f32, vp, vp, vp, _c.c_size_t,
                                     vp]
+        L.ftts_linear_plan.restype = _c.c_int
+        L.ftts_linear_plan.argtypes = [i32, i32, i32, i32, P(LinearShape)]
         _lib = L
     return _lib
 
@@ -168,6 +175,13 @@ def workspace_bytes(cfg: Config, max_batch: int, max_rows: int = 0) -> int:
     if n == 0:
         raise FTTSError(-1, lib().ftts_last_error().decode())
     return n
+
+
+def linear_plan(wdtype: int, rows: int, N: int, K: int) -> LinearShape:
+    """ftts_linear_plan: how a prefill or DiT linear of that shape is launched (host only)."""
+    out = LinearShape()
+    _check(lib().ftts_linear_plan(wdtype, rows, N, K, _c.byref(out)))
+    return out
 
 
 def quantize_weights(wdtype: int, w, codes, scales, zeros=None, group_size: int = 128, stream=None):
