@@ -25,6 +25,7 @@
 //
 // FTTS_F32 mode has a plain fp32 kernel (gemm.hip).
 #include <algorithm>
+#include <atomic>
 
 #include "gemm_epilogue.hpp"
 
@@ -375,10 +376,18 @@ static hipError_t small_launch(const GemmArgs& a, int splits, hipStream_t st) {
     const int tiles = ((a.M + kSgM - 1) / kSgM) * ((a.N + BN - 1) / BN);
     const int steps = a.K / SH::KS, nk = (steps + splits - 1) / splits;
     const size_t lds = std::max<size_t>((size_t)SH::S * SH::STAGE + (WT == FTTS_W4A16 ? (size_t)BN * nk * 4 : 0), 4 * 4096);
-    if (lds > 65536) {
-        static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_small_kernel<WT, EPI, BN>),
-                                                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        if (raised != hipSuccess) return raised;
+    if (lds > 65536) {  // the limit is raised once per instantiation and device
+        static std::atomic<uint64_t> raised{0};
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        const uint64_t bit = 1ull << (dev & 63);
+        if (dev >= 64 || !(raised.load(std::memory_order_relaxed) & bit)) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_small_kernel<WT, EPI, BN>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+            if (e != hipSuccess) return e;
+            raised.fetch_or(bit, std::memory_order_relaxed);
+        }
     }
     hipLaunchKernelGGL((gemm_small_kernel<WT, EPI, BN>), dim3(tiles, splits), dim3(kSgThreads), lds, st, a);
     return hipGetLastError();
