@@ -289,18 +289,21 @@ hipError_t launch_assemble_prefix(int wdtype, const AssembleArgs& a, int rows, h
 // indices t, t + 1024, ... in registers.  Order is by (value, index): the larger
 // value first, the lower index on ties.  NaN logits count as -inf.
 //
-// Top-k without k sequential block reductions.  If t is the k-th largest of the 256
-// maxima over groups of four lanes, at least k entries are >= t, so every one of the k
-// best is, and few others are (about 32 in all for k = 30 and spread-out logits).
-// t is found by counting, one thread per group maximum; the finite entries >= t are
-// collected in LDS as 64-bit keys that sort by (value, index), each is ranked by
+// Top-k without k sequential block reductions.  If t is the k-th largest of the maxima
+// over disjoint groups of entries, at least k entries are >= t, so every one of the k
+// best is, and few others are.  The groups are the 16 waves where k is at most 16 and the
+// row reaches k of them (each wave finds t by itself after one barrier), else 256 groups
+// of four lanes (counted by one thread each; about 32 entries in all for k = 30 and spread-out
+// logits); rows of up to kSampShort entries take t = -inf.  The entries >= t and above -inf
+// are collected in LDS as 64-bit keys that sort by (value, index), each is ranked by
 // counting the keys above it, and ranks below k fill the ordered top-k list.  Where
-// fewer than k groups hold an entry above -inf (a row of fewer than 4 k entries, or one
-// masked to a short run), t is -inf and every entry above -inf is collected; if these are fewer
-// than k, the lowest-index -inf entries take the ranks after them (32 rows, k = 30: 100
-// entries 9.6 us, 8194 masked to a run of 90 10.4 us; by rounds of argmax 50 and 57).  Rows with more than
-// kSampCand candidates (massive exact ties, or more entries than that in fewer than k
-// groups) take k rounds of block argmax instead.
+// fewer than k groups hold an entry above -inf (a row masked to a short run), t is -inf;
+// if the entries above -inf are fewer than k, the lowest-index -inf entries take the
+// ranks after them.  Rows with more than kSampCand candidates (massive exact ties, or
+// more entries than that in fewer than k groups) take k rounds of block argmax instead.
+// Measured, us: 32 rows at k = 30, 100 entries 9.1 and 8194 masked to a run of 90 10.4 (by
+// rounds of argmax 50 and 57); 1024 rows of 16384 at k = 2 17.5 by the waves' maxima, 24.8
+// by the 256 groups'; 32 rows of 8194 at k = 10 9.0 and 9.6.
 //
 // A row is 33 KB, so the kernel is bound by its chain of short steps: with 256 threads
 // (64 entries each, 33 divisions of them in use, a per-wave threshold that let about
@@ -308,6 +311,7 @@ hipError_t launch_assemble_prefix(int wdtype, const AssembleArgs& a, int rows, h
 // at k = 30; now 10.9 us.
 constexpr int kSampThreads = 1024, kSampWaves = kSampThreads / kWave, kSampPer = 16;  // vocab <= 16384
 constexpr int kSampCand = 1024;
+constexpr int kSampShort = 256;  // rows of up to this many entries are ranked whole
 
 __device__ __forceinline__ bool beats(float v, int i, float bv, int bi) {
     return v > bv || (v == bv && i < bi);
@@ -373,6 +377,27 @@ __device__ __forceinline__ void block_best(float& v, int& i, float* rv, int* ri)
     __syncthreads();
 }
 
+// How many of the n values v (16-byte aligned) are above, and at or above, own.
+template <int n>
+__device__ __forceinline__ void count_above(const float* v, float own, int& gt, int& ge) {
+    const float4* v4 = reinterpret_cast<const float4*>(v);
+#pragma unroll 8
+    for (int c = 0; c < n / 4; ++c) {
+        const float4 o = v4[c];
+        gt += (o.x > own) + (o.y > own) + (o.z > own) + (o.w > own);
+        ge += (o.x >= own) + (o.y >= own) + (o.z >= own) + (o.w >= own);
+    }
+}
+// The k-th largest of n values, in every lane (lane i looks at value `at` = i % n).
+template <int n>
+__device__ __forceinline__ float kth_largest(const float* v, int at, int k) {
+    const float own = v[at];
+    int gt = 0, ge = 0;
+    count_above<n>(v, own, gt, ge);
+    const uint64_t hit = __ballot(gt < k && k <= ge);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own), (int)__builtin_ctzll(hit)));
+}
+
 __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logits, int V, float temperature,
                                                               int top_k, float top_p, const float* uniforms,
                                                               const int32_t* active, int32_t* out) {
@@ -380,7 +405,7 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
     __shared__ __attribute__((aligned(16))) uint64_t s_key[kSampCand + 8];
     __shared__ float selv[FTTS_MAX_TOP_K];
     __shared__ int seli[FTTS_MAX_TOP_K];
-    __shared__ float rv[kSampWaves];
+    __shared__ __attribute__((aligned(16))) float rv[kSampWaves];
     __shared__ int ri[kSampWaves];
     __shared__ int s_cnt;
     __shared__ float s_t;
@@ -417,25 +442,31 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
     float lm = -INFINITY;
 #pragma unroll
     for (int j = 0; j < kSampPer; ++j) lm = fmaxf(lm, z[j]);
-    {
-        const float gm = group_max<4>(lm);
-        if ((lane & 3) == 0) s_gm[tid >> 2] = gm;
-    }
-    __syncthreads();
-    if (tid < kSampThreads / 4) {
-        const float own = s_gm[tid];
-        int gt = 0, ge = 0;
-        const float4* g4 = reinterpret_cast<const float4*>(s_gm);
-#pragma unroll 8
-        for (int c = 0; c < kSampThreads / 16; ++c) {
-            const float4 o = g4[c];
-            gt += (o.x > own) + (o.y > own) + (o.z > own) + (o.w > own);
-            ge += (o.x >= own) + (o.y >= own) + (o.z >= own) + (o.w >= own);
+    float t = -INFINITY;
+    if (V <= kSampShort) {
+        __syncthreads();
+    } else {
+        if (top_k <= min(kSampWaves, V / kWave)) {
+            const float wm = wave_max(lm);
+            if (lane == 0) rv[wave] = wm;
+            __syncthreads();
+            t = kth_largest<kSampWaves>(rv, lane & (kSampWaves - 1), top_k);
         }
-        if (gt < top_k && top_k <= ge) s_t = own;  // (every thread that writes holds the same value)
+        if (t == -INFINITY) {  // (uniform over the workgroup)
+            const float gm = group_max<4>(lm);
+            if ((lane & 3) == 0) s_gm[tid >> 2] = gm;
+            __syncthreads();
+            if (tid < kSampThreads / 4) {
+                const float own = s_gm[tid];
+                int gt = 0, ge = 0;
+                count_above<kSampThreads / 4>(s_gm, own, gt, ge);
+                if (gt < top_k && top_k <= ge) s_t = own;  // (every thread that writes holds the same value)
+            }
+            __syncthreads();
+            t = s_t;
+        }
     }
-    __syncthreads();
-    const float t = fmaxf(s_t, -FLT_MAX);  // (neither the slots past the row nor masked entries compete)
+    t = fmaxf(t, -FLT_MAX);  // (neither the slots past the row nor masked entries compete)
     if (lm >= t) {
 #pragma unroll
         for (int j = 0; j < kSampPer; ++j)
