@@ -18,7 +18,7 @@
 // flow-matching DiT's frames all see each other).  16-bit activations run on the
 // matrix cores: attn_tile.hip, whose waves share each key tile on wide grids and split the
 // keys of a 32-query tile on short ones.  A wave forms
-// S^T = K Q^T (keys as rows, so every lane ends up holding 16 scores of its own query),
+// S^T = K Q^T (keys as rows, so every lane ends up holding 32 scores of its own query),
 // applies the online softmax per lane, and accumulates O^T = V^T P^T with the
 // probabilities taken straight from its score registers: the MFMA k order is a
 // permutation shared by both operands, so P needs no reshuffle.  fp32 activations keep
@@ -401,7 +401,13 @@ __global__ __launch_bounds__(64) void attn_prefill_kernel(const AttnPrefillArgs 
         st_act<F32>(a.o, (size_t)(row0 + qi) * a.d_model + h * kHeadDim + j, o[j] * inv);
 }
 
-int prefill_tile_rows(int) { return 64; }  // (fp32; the 16-bit launcher tiles by itself)
+// Query tiles of q rows per sequence; returns their number.
+static int set_tiles(AttnPrefillArgs& a, int q) {
+    a.tiles_cu[0] = 0;
+    for (int i = 0; i < a.seqs.n; ++i)
+        a.tiles_cu[i + 1] = a.tiles_cu[i] + (a.seqs.cu[i + 1] - a.seqs.cu[i] + q - 1) / q;
+    return a.tiles_cu[a.seqs.n];
+}
 
 // 128-query tiles that share each key tile (attn_tile.hip) once they give at least one
 // workgroup per compute unit, else 32-query tiles with the keys split over the waves, so
@@ -409,22 +415,18 @@ int prefill_tile_rows(int) { return 64; }  // (fp32; the 16-bit launcher tiles b
 static hipError_t launch_attn_bf16(bool causal, const AttnPrefillArgs& a, hipStream_t st) {
     constexpr int kFillGroups = 256;
     AttnPrefillArgs b = a;
-    auto tiles = [&](int q) {
-        b.tiles_cu[0] = 0;
-        for (int i = 0; i < a.seqs.n; ++i)
-            b.tiles_cu[i + 1] = b.tiles_cu[i] + (a.seqs.cu[i + 1] - a.seqs.cu[i] + q - 1) / q;
-        return b.tiles_cu[a.seqs.n];
-    };
-    const int wide = tiles(attn_tile_queries());
+    const int wide = set_tiles(b, attn_tile_queries());
     if (wide == 0) return hipSuccess;
     if ((long)wide * a.n_head >= kFillGroups) return launch_attn_tile(causal, b, wide, st);
-    const int split = tiles(attn_split_queries());
+    const int split = set_tiles(b, attn_split_queries());
     return launch_attn_split(causal, b, split, st);
 }
 
-hipError_t launch_attn_prefill(int wdtype, const AttnPrefillArgs& a, int total_tiles, hipStream_t st) {
+hipError_t launch_attn_prefill(int wdtype, const AttnPrefillArgs& a, hipStream_t st) {
     if (wdtype != FTTS_F32) return launch_attn_bf16(true, a, st);
-    hipLaunchKernelGGL(attn_prefill_kernel<true>, dim3(total_tiles, a.n_head), dim3(64), 0, st, a);
+    AttnPrefillArgs b = a;
+    const int tiles = set_tiles(b, 64);
+    hipLaunchKernelGGL(attn_prefill_kernel<true>, dim3(tiles, a.n_head), dim3(64), 0, st, b);
     return hipGetLastError();
 }
 

@@ -58,25 +58,18 @@ constexpr int kLnGroups = kBgemmThreads / kBgemmRows;
 constexpr int kLnMaxTP = 8;                                  // tiles per group: K <= 2048
 constexpr int kLnMaxK = kLnGroups * kLnMaxTP * kStatTile;
 
-
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {  // one packed conversion
     const bgemm_bf16x2 v = {(__bf16)lo, (__bf16)hi};
     return __builtin_bit_cast(uint32_t, v);
 }
 
-template <int WT, bool LN>
-__device__ __forceinline__ void load_chunk(const BgemmArgs& p, int n, int m, int h, int c, BChunk<WT>& ch) {
-    using C = BChunk<WT>;
-    const int nn = min(n, p.N - 1);
-    const int ka = c * C::KC + h * (C::KC / 2);
-    // Every load is unconditional (rows past the batch read the last row and are
-    // zeroed afterwards), so the loads of all chunks stay in flight together.
-    const int mr = min(m, p.B - 1);
-    (void)mr;
-    (void)ka;
+// The scale and zero-point of feature n in group c (W4A16; the operands themselves are staged).
+template <int WT>
+__device__ __forceinline__ void load_group(const BgemmArgs& p, int n, int c, BChunk<WT>& ch) {
     if constexpr (WT == FTTS_W4A16) {
-        ch.s = bf16_to_f32(p.scale[(size_t)nn * (p.K / 128) + c]);
-        ch.z = bf16_to_f32(p.zero[(size_t)nn * (p.K / 128) + c]);
+        const size_t at = (size_t)min(n, p.N - 1) * (p.K / 128) + c;
+        ch.s = bf16_to_f32(p.scale[at]);
+        ch.z = bf16_to_f32(p.zero[at]);
     }
 }
 
@@ -242,7 +235,7 @@ __global__ __launch_bounds__(kBgemmThreads) void bgemm_kernel(const BgemmArgs p)
     else stage_act<WT>(p, cw0, s_xs[wave]);
     C ch[CPW];
 #pragma unroll
-    for (int j = 0; j < CPW; ++j) load_chunk<WT, LN>(p, n0 + fr, fr, h, min(cw0 + j, c1 - 1), ch[j]);
+    for (int j = 0; j < CPW; ++j) load_group<WT>(p, n0 + fr, min(cw0 + j, c1 - 1), ch[j]);
     // Nothing that waits for a load may be scheduled above this point: every load
     // above is in flight before the first wait.
     __builtin_amdgcn_sched_barrier(0);

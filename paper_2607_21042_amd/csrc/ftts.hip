@@ -678,7 +678,6 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
     AttnPrefillArgs ap{};
     seqs.n = B;
     seqs.cu[0] = 0;
-    ap.tiles_cu[0] = 0;
     int64_t M = 0;
     for (int b = 0; b < B; ++b) {
         if (lens[b] < 1) return fail(FTTS_E_RANGE, "lens[%d] = %d must be >= 1", b, lens[b]);
@@ -687,7 +686,6 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
         M += lens[b];
         if (M > (1 << 24)) return fail(FTTS_E_RANGE, "total prefix rows too large");
         seqs.cu[b + 1] = (int)M;
-        ap.tiles_cu[b + 1] = ap.tiles_cu[b] + (lens[b] + prefill_tile_rows(c.wdtype) - 1) / prefill_tile_rows(c.wdtype);
     }
     PrefillWs P;
     const size_t need = prefill_bytes(c, B, (int)M, &P, reinterpret_cast<char*>(ws));
@@ -726,8 +724,6 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
     kva.n_pages = kv->n_pages;
     kva.n_head = c.n_head;
     kva.d_model = d;
-    kva.max_pages = pt->max_pages;
-    kva.block_table = pt->block_table;
     kva.slots = P.slots;
 
     ap.qkv = P.qkv;
@@ -765,7 +761,6 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
         g.out = P.qkv;
         g.kv = kva;
         g.kv.layer = l;
-        g.seqs = seqs;
         if ((e = launch_gemm(c.wdtype, EPI_QKV, g, p_qkv, st)) != hipSuccess) return hip_fail(e, "qkv gemm");
         if (last) {
             if (!last_logits) break;
@@ -773,7 +768,7 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
             if ((e = launch_gather_rows(P.x, d, seqs, P.xlast, st)) != hipSuccess) return hip_fail(e, "gather");
             x = P.xlast;
             g.M = B;
-        } else if ((e = launch_attn_prefill(c.wdtype, ap, ap.tiles_cu[B], st)) != hipSuccess) {
+        } else if ((e = launch_attn_prefill(c.wdtype, ap, st)) != hipSuccess) {
             return hip_fail(e, "prefill attention");
         }
         auto plan = [&](const GemmPlan& p) { return last ? gemm_plan(c.wdtype, B, g.N, g.K) : p; };

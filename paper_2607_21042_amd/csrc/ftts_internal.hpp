@@ -151,7 +151,8 @@ enum Epi { EPI_STORE = 0, EPI_QKV = 1, EPI_GELU = 2, EPI_RESID = 3 };
 
 struct KvAppend {            // where the QKV epilogue writes keys and values
     void* base;
-    int n_pages, layer, n_head, d_model, max_pages;
+    int n_pages, layer, n_head, d_model;
+    int max_pages;           // decode: row length of the page table
     const int32_t* block_table;
     const int32_t* seq_lens;  // decode: slot = seq_lens[b]
     const int32_t* active;    // decode: per-row flag
@@ -232,8 +233,7 @@ struct GemmArgs {
     const void* bias;
     int M, N, K;
     void* out;               // STORE/QKV/GELU: [M][N] activation dtype; RESID: fp32 [M][N] in place
-    KvAppend kv;             // QKV epilogue (prefill form: slot = position within the sequence)
-    SeqTable seqs;
+    KvAppend kv;             // QKV epilogue (prefill form: KvAppend::slots)
     float* part;             // split K: [S] fp32 partial tiles of whole 64 x bn blocks
     uint32_t* count;         // split K: per-tile arrival counters, zero between calls
     size_t part_floats;      // how much of each there is
@@ -255,7 +255,7 @@ struct AttnPrefillArgs {
     void* o;                 // [M][d] activation dtype
     int d_model, n_head;
     SeqTable seqs;
-    int tiles_cu[kMaxPrefillSeqs + 1];  // prefix sums of query tiles (prefill_tile_rows) per sequence
+    int tiles_cu[kMaxPrefillSeqs + 1];  // prefix sums of query tiles per sequence (set by the launchers)
 };
 
 // Prefill input assembly: sequence b's rows are its cond_lens[b] conditioning
@@ -290,10 +290,9 @@ hipError_t launch_ln_rows(int wdtype, const float* x, const void* g, const void*
 hipError_t launch_gemm(int wdtype, int epi, const GemmArgs& a, const GemmPlan& p, hipStream_t st);  // p unused in fp32
 hipError_t launch_gemm_large(int epi, const GemmArgs& a, int mt, int nt, hipStream_t st);
 hipError_t launch_gemm_small(int wdtype, int epi, const GemmArgs& a, int bn, int splits, hipStream_t st);
-hipError_t launch_attn_prefill(int wdtype, const AttnPrefillArgs& a, int total_tiles, hipStream_t st);
-int prefill_tile_rows(int wdtype);  // queries per prefill-attention workgroup
-// Attention without a mask (every query sees every key of its sequence), bf16; the
-// launcher sets its own query tiling (tiles_cu of `a` is ignored).
+// Causal attention of every row, and (bf16) attention without a mask (every query sees
+// every key of its sequence).
+hipError_t launch_attn_prefill(int wdtype, const AttnPrefillArgs& a, hipStream_t st);
 hipError_t launch_attn_full_bf16(const AttnPrefillArgs& a, hipStream_t st);
 // bf16 attention in workgroups of attn_tile_queries() queries (tiles_cu counts them), `tiles` in all.
 hipError_t launch_attn_tile(bool causal, const AttnPrefillArgs& a, int tiles, hipStream_t st);
