@@ -1,10 +1,13 @@
 """Launch shapes of the prefill and DiT linears (CPU, ftts_linear_plan): the split-K
 scratch that a workspace holds covers the plan of every row count up to the one it was
-sized for, and a model whose linears never split has none of it.
+sized for, and a model whose linears never split has none of it.  And the cases of
+tests/test_gpu_gemm.py reach every launch shape that the widths they use give, by
+epilogue, so that a change of the plan that leaves one untested fails here.
 """
 import pytest
 
 from paper_2607_21042_amd import ftts, workload
+from tests import test_gpu_gemm as cases
 
 SHAPES = [workload.INDEXTTS2, workload.TINY,
           workload.ModelShape(n_layer=1, d_model=4096, n_head=64, d_head=64, d_ff=16384, vocab=640)]
@@ -65,3 +68,38 @@ def test_linear_plan_argument_errors():
         with pytest.raises(ftts.FTTSError) as e:
             ftts.linear_plan(*args)
         assert e.value.code == code, args
+
+
+def launches(shape, wdtype, rows):
+    """(mode, epilogue, kernel, its tile or columns, K split) of every launch of the linears at so many rows."""
+    dit = hasattr(shape, "n_mel")
+    epilogue = {"qkv": "store" if dit else "qkv", "fc1": "gelu"}
+    out = set()
+    for name, N, K in linears(shape):
+        e, p = epilogue.get(name, "residual"), ftts.linear_plan(wdtype, rows, N, K)
+        if p.rows_large:
+            out.add((wdtype, e, "large", p.large_rows, p.large_cols))
+        if p.small_cols:
+            out.add((wdtype, e, "small", p.small_cols, p.splits > 1))
+        if p.rows_large and p.small_cols:
+            out.add((wdtype, e, "large, rest small"))
+    return out
+
+
+def test_gemm_cases_reach_every_launch_shape():
+    wd = {"bf16": ftts.BF16, "w8a16": ftts.W8A16, "w4a16": ftts.W4A16}
+    reached, reachable = set(), set()
+    for shape, prefills in ((cases.SHAPE, cases.PREFILLS), (cases.SHAPE_640, cases.PREFILLS_640)):
+        assert shape.n_layer >= 2  # all rows of a prefill pass every linear of a layer before the last
+        for mode, lens in prefills:
+            reached |= launches(shape, wd[mode], sum(lens)) | launches(shape, wd[mode], len(lens))
+        for mode in {m for m, _ in prefills}:
+            for rows in range(8, 12001, 32):
+                reachable |= launches(shape, wd[mode], rows)
+    for shape, steps in ((cases.DIT, cases.DITS), (cases.DIT_640, cases.DITS_640)):
+        for lens in steps:
+            reached |= launches(shape, ftts.BF16, 2 * sum(lens))
+        for rows in range(16, 12001, 32):
+            reachable |= launches(shape, ftts.BF16, rows)
+    assert len(reachable) > 40
+    assert not reachable - reached, sorted(reachable - reached, key=str)
