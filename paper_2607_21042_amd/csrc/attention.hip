@@ -23,6 +23,8 @@
 // probabilities taken straight from its score registers: the MFMA k order is a
 // permutation shared by both operands, so P needs no reshuffle.  fp32 activations keep
 // a VALU kernel: one thread per query row streams 64-key tiles of K and V through LDS.
+#include <algorithm>
+
 #include "kv_page.hpp"
 
 namespace ftts {
@@ -409,15 +411,29 @@ static int set_tiles(AttnPrefillArgs& a, int q) {
     return a.tiles_cu[a.seqs.n];
 }
 
-// 128-query tiles that share each key tile (attn_tile.hip) once they give at least one
-// workgroup per compute unit, else 32-query tiles with the keys split over the waves, so
-// that a query tile's dependent chain is a quarter of its keys.
+// Workgroups of 128 queries whose waves share each key tile (attn_tile.hip), or of 32
+// whose waves split the keys.  The first reads a key tile a quarter as often, but walks
+// the c = ceil(length / 64) tiles of a sequence in one chain, four times as long; so it
+// needs enough workgroups g that the chip is busy while the longest chain runs.  Fitted to 214
+// calls of both kernels (causal with 20, 8 and 4 heads, unmasked with 12 and 4; 1 to
+// 28 sequences of 60 to 24,000 rows): they cross at about 24 workgroups per tile of the
+// longest chain, for short sequences not before half a workgroup per compute unit, and at
+// the latest where the workgroups fill the chip (768, three a unit).  Tile minus split kernel,
+// us a layer: 20 heads, 3 / 4 x 300 rows (g 180 / 240, c 5) -2.8 / -3.3, 2 x 500 (160, c 8)
+// +0.2, 3 x 500 (240) -2.3, one of 1500 (240, c 24) +6.2, 3000 (480, c 47) +1.7, 16,000
+// (2500, c 250) -15; 12 heads unmasked, both branches, 500 frames (96, c 8) +2.7, 2 x 500
+// (192) -1.1, 8 x 120 (192, c 2) -3.4, 1500 (288, c 24) +4.1.  Taking the worse of the two
+// costs 0.3% of a call on average by this rule, 1.1% by a line at 256 workgroups.
 static hipError_t launch_attn_bf16(bool causal, const AttnPrefillArgs& a, hipStream_t st) {
-    constexpr int kFillGroups = 256;
+    constexpr int kPerTile = 24, kLeast = 128, kFull = 768;
     AttnPrefillArgs b = a;
     const int wide = set_tiles(b, attn_tile_queries());
     if (wide == 0) return hipSuccess;
-    if ((long)wide * a.n_head >= kFillGroups) return launch_attn_tile(causal, b, wide, st);
+    int longest = 0;
+    for (int i = 0; i < a.seqs.n; ++i) longest = std::max(longest, a.seqs.cu[i + 1] - a.seqs.cu[i]);
+    const int chain = (longest + 63) / 64;
+    if ((long)wide * a.n_head >= std::min(std::max(kPerTile * chain, kLeast), kFull))
+        return launch_attn_tile(causal, b, wide, st);
     const int split = set_tiles(b, attn_split_queries());
     return launch_attn_split(causal, b, split, st);
 }

@@ -1,9 +1,10 @@
 """GPU parity of the 16-bit attention at the edges of its tiles: sequence lengths
 on both sides of the 64-key tile, the 32-query and 128-query tiles and one and
 two rounds of the key split, with and without the mask, packed into a short grid
-(the keys of a query tile split over waves) and a wide one (at least 256
-workgroups of 128 queries).  Through the public calls; bars as in
-tests/helpers.py (bf16 storage: 3e-2 absolute on logits; DiT: its own).
+(the keys of a query tile split over waves) and a wide one (key tiles shared by 128
+queries; `wide` below is the launcher's rule), and at the edges of the rule between
+them.  Through the public calls; bars as in tests/helpers.py (bf16 storage: 3e-2
+absolute on logits; DiT: its own).
 """
 import numpy as np
 import pytest
@@ -16,8 +17,14 @@ from tests import helpers
 pytestmark = pytest.mark.gpu
 
 EDGES = [1, 31, 32, 33, 63, 64, 65, 95, 96, 97, 127, 128, 129, 191, 193, 255, 256, 257, 320, 321]
-# (heads, lengths): 20 sequences give fewer than 256 tiles of 128 queries at 4 heads, more at 8
+# (heads, lengths): the causal calls take the short grid at 4 heads and the wide one at 8
 SHORT, WIDE = (4, EDGES), (8, EDGES + EDGES[::-1])
+
+
+def wide(lens, n_head):
+    """Whether so many sequences (a DiT step: both branches) take 128-query workgroups."""
+    groups = sum(-(-n // 128) for n in lens) * n_head
+    return groups >= min(max(24 * -(-max(lens) // 64), 128), 768)
 
 
 @pytest.mark.parametrize("n_head,lens", [SHORT, WIDE])
@@ -27,7 +34,7 @@ def test_causal_attention_edges(n_head, lens):
     from paper_2607_21042_amd import ftts
     lens = lens[:32]
     shape = workload.ModelShape(n_layer=2, d_model=64 * n_head, n_head=n_head, d_head=64, d_ff=512, vocab=640)
-    assert (sum(-(-n // 128) for n in lens) * n_head >= 256) == (n_head == 8)
+    assert wide(lens, n_head) == (n_head == 8)
     inputs = workload.bf16_weights(workload.master_weights(shape, seed=3))
     dm = ftts.DeviceModel(inputs, shape, ftts.BF16)
     rows = workload.prefix_embeddings(lens, shape.d_model, seed=17)
@@ -43,7 +50,40 @@ def test_causal_attention_edges(n_head, lens):
             assert ok, (n_head, lens[b], err)
 
 
-@pytest.mark.parametrize("n_head,lens", [SHORT, WIDE])
+def test_the_cases_take_both_grids():
+    assert [wide(2 * lens[:32], n_head) for n_head, lens in FULL] == [True, True, False, False]
+    assert [wide(lens, n_head) for n_head, lens in RULE_EDGES] == [False, True] * 3
+
+
+# (heads, lengths) of the unmasked calls: wide, wide, short, short
+FULL = [SHORT, WIDE, (4, EDGES[::2]), (4, EDGES[1::2])]
+
+
+# both sides of the rule's three lines: 24 groups per 64 keys of the longest sequence, 128, 768
+RULE_EDGES = [(8, [500] * 5 + [300]), (8, [500] * 6), (8, [100] * 15), (8, [100] * 16),
+              (8, [128 * 41] + [128] * 54), (8, [128 * 41] + [128] * 55)]
+
+
+@pytest.mark.parametrize("n_head,lens", RULE_EDGES)
+def test_causal_attention_around_the_rule(n_head, lens):
+    from paper_2607_21042_amd import ftts
+    shape = workload.ModelShape(n_layer=2, d_model=64 * n_head, n_head=n_head, d_head=64, d_ff=512, vocab=640)
+    inputs = workload.bf16_weights(workload.master_weights(shape, seed=3))
+    dm = ftts.DeviceModel(inputs, shape, ftts.BF16)
+    rows = workload.prefix_embeddings(lens, shape.d_model, seed=17)
+    prefixes = np.split(rows, np.cumsum(lens)[:-1])
+    fed = workload.random_tokens(1, len(lens), shape.vocab, seed=5)
+    print(f"causal attention around the rule: {n_head} heads, {len(lens)} prefixes", flush=True)
+    res = helpers.run_gpu(dm, shape, prefixes, fed)
+    model = ogpt.GPT(helpers.oracle_weights(inputs, "bf16"), shape.n_head, shape.d_head)
+    for b in sorted({0, 1, len(lens) // 2, len(lens) - 1}):
+        last, dec = helpers.oracle_teacher_forced(model, prefixes[b], fed[:, b])
+        for got, ref in ((res["prefill"][b], last), (res["logits"][0, b], dec[0])):
+            ok, err = helpers.tolerance_ok(got, ref, "bf16")
+            assert ok, (n_head, lens[b], err)
+
+
+@pytest.mark.parametrize("n_head,lens", FULL)
 def test_full_attention_edges(n_head, lens):
     import torch
     from paper_2607_21042_amd import ftts
@@ -100,7 +140,7 @@ def test_non_finite_rows_stay_causal(n_head, seqs):
     shape = workload.ModelShape(n_layer=3, d_model=64 * n_head, n_head=n_head, d_head=64, d_ff=512, vocab=640)
     dm = ftts.DeviceModel(workload.bf16_weights(workload.master_weights(shape, seed=3)), shape, ftts.BF16)
     lens = [230] * seqs
-    assert (seqs * 2 * n_head >= 256) == (n_head == 8)
+    assert wide(lens, n_head) == (n_head == 8)
     table, n_pages = helpers.make_block_table(lens)
     pt = ftts.PageTableView(torch.from_numpy(table).cuda(), torch.zeros(seqs, dtype=torch.int32, device="cuda"))
     clean = torch.from_numpy(workload.prefix_embeddings(lens, shape.d_model, seed=17)).cuda().to(torch.bfloat16)
