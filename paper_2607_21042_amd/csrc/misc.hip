@@ -291,26 +291,27 @@ hipError_t launch_assemble_prefix(int wdtype, const AssembleArgs& a, int rows, h
 //
 // Top-k without k sequential block reductions.  If t is the k-th largest of the maxima
 // over disjoint groups of entries, at least k entries are >= t, so every one of the k
-// best is, and few others are.  The groups are the 16 waves where k is at most 16 and the
-// row reaches k of them (each wave finds t by itself after one barrier), else 256 groups
-// of four lanes (counted by one thread each; about 32 entries in all for k = 30 and spread-out
-// logits); rows of up to kSampShort entries take t = -inf.  The entries >= t and above -inf
-// are collected in LDS as 64-bit keys that sort by (value, index), each is ranked by
-// counting the keys above it, and ranks below k fill the ordered top-k list.  Where
-// fewer than k groups hold an entry above -inf (a row masked to a short run), t is -inf;
-// if the entries above -inf are fewer than k, the lowest-index -inf entries take the
-// ranks after them.  Rows with more than kSampCand candidates (massive exact ties, or
-// more entries than that in fewer than k groups) take k rounds of block argmax instead.
-// Measured, us: 32 rows at k = 30, 100 entries 9.1 and 8194 masked to a run of 90 10.4 (by
-// rounds of argmax 50 and 57); 1024 rows of 16384 at k = 2 17.5 by the waves' maxima, 24.8
-// by the 256 groups'; 32 rows of 8194 at k = 10 9.0 and 9.6.
+// best is, and few others are.  The fewer the groups, the shorter the count that finds
+// t, and the more candidates it lets through; so, where the row reaches k of them, the 16
+// waves serve k <= 16 and 64 groups of 16 lanes k <= 32 (every wave finds t by itself
+// after one barrier), else 256 groups of four lanes (one thread each and a second
+// barrier; about 32 candidates for k = 30 and spread-out logits).  The entries >= t and
+// above -inf are collected in LDS as 64-bit keys that sort by (value, index), each is
+// ranked by counting the keys above it, and ranks below k fill the ordered top-k list.
+// t = -inf, all entries above -inf, serves rows of up to kSampShort entries and rows masked
+// so that few threads hold one; if there are fewer than k, the lowest-index -inf
+// entries take the ranks after them.  Rows with more than kSampCand candidates (massive
+// exact ties, or many entries in few groups) take k rounds of block argmax instead.
 //
-// A row is 33 KB, so the kernel is bound by its chain of short steps: with 256 threads
-// (64 entries each, 33 divisions of them in use, a per-wave threshold that let about
-// 180 candidates through, ranked one LDS read at a time) 32 rows of 8194 took 23.7 us
-// at k = 30; now 10.9 us.
+// A row is 33 KB, so the kernel is bound by its chain of short steps.  Measured, us a call:
+// 32 rows of 8194 at k = 30: 8.2 (10.2 with 256 groups for every k; 24 with 256 threads, a threshold per
+// wave that let about 180 candidates through, ranked one LDS read at a time); at k = 10
+// 8.9 (9.9 with 256 groups), k = 64 12.0; 100 entries 7.8 and 8194 masked to a run of 90 8.6 at
+// k = 30 (50 and 57 by rounds of argmax); 1024 rows of 16384, bound by reading them, 14.0
+// greedy and 17.0 at k = 2 (25.1 with 256 groups).
 constexpr int kSampThreads = 1024, kSampWaves = kSampThreads / kWave, kSampPer = 16;  // vocab <= 16384
 constexpr int kSampCand = 1024;
+constexpr int kSampFew = 128;     // as are all entries above -inf of a masked row if no more threads than this hold one
 constexpr int kSampShort = 256;  // rows of up to this many entries are ranked whole
 
 __device__ __forceinline__ bool beats(float v, int i, float bv, int bi) {
@@ -398,6 +399,46 @@ __device__ __forceinline__ float kth_largest(const float* v, int at, int k) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own), (int)__builtin_ctzll(hit)));
 }
 
+// This thread's entries of a row: tempered logits (GREEDY: as they are), NaN as -inf,
+// -inf past the row.  The row, the draw and the activity flag are requested together;
+// false if the sequence is not active.
+template <bool GREEDY>
+__device__ __forceinline__ bool sample_load(const float* row, int V, float temperature, const float* uniform,
+                                            const int32_t* active, float (&z)[kSampPer], float& u) {
+#pragma unroll
+    for (int j = 0; j < kSampPer; ++j) {
+        const int i = (int)threadIdx.x + kSampThreads * j;
+        z[j] = i < V ? row[i] : -INFINITY;
+    }
+    u = GREEDY ? 0.f : *uniform;
+    if (active && !*active) return false;
+#pragma unroll
+    for (int j = 0; j < kSampPer; ++j) {
+        if (kSampThreads * j >= V) continue;  // uniform: slots past the row stay -inf
+        const float v = GREEDY ? z[j] : z[j] / temperature;
+        z[j] = v != v ? -INFINITY : v;
+    }
+    return true;
+}
+
+__global__ __launch_bounds__(kSampThreads) void greedy_kernel(const float* logits, int V, const int32_t* active,
+                                                              int32_t* out) {
+    __shared__ float rv[kSampWaves];
+    __shared__ int ri[kSampWaves];
+    const int b = blockIdx.x, tid = threadIdx.x;
+    float z[kSampPer], u, bv;
+    int bi;
+    if (!sample_load<true>(logits + (size_t)b * V, V, 1.f, nullptr, active ? active + b : nullptr, z, u)) {
+        if (tid == 0) out[b] = -1;
+        return;
+    }
+    lane_best(z, 0, bv, bi);
+    block_best(bv, bi, rv, ri);
+    if (tid == 0) out[b] = bi < V ? bi : 0;
+}
+
+// G: the groups whose maxima are tried first.
+template <int G>
 __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logits, int V, float temperature,
                                                               int top_k, float top_p, const float* uniforms,
                                                               const int32_t* active, int32_t* out) {
@@ -405,38 +446,15 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
     __shared__ __attribute__((aligned(16))) uint64_t s_key[kSampCand + 8];
     __shared__ float selv[FTTS_MAX_TOP_K];
     __shared__ int seli[FTTS_MAX_TOP_K];
-    __shared__ __attribute__((aligned(16))) float rv[kSampWaves];
+    __shared__ float rv[kSampWaves];
     __shared__ int ri[kSampWaves];
     __shared__ int s_cnt;
     __shared__ float s_t;
     const int b = blockIdx.x, tid = threadIdx.x, wave = tid / kWave, lane = tid & (kWave - 1);
-    const float* row = logits + (size_t)b * V;
-    const bool greedy = top_k == 1;
-    // the row, the draw and the activity flag are requested together
-    float z[kSampPer];
-#pragma unroll
-    for (int j = 0; j < kSampPer; ++j) {
-        const int i = tid + kSampThreads * j;
-        z[j] = i < V ? row[i] : -INFINITY;
-    }
+    float z[kSampPer], u;
     if (tid == 0) s_cnt = 0;
-    const float u = greedy ? 0.f : uniforms[b];
-    if (active && !active[b]) {
+    if (!sample_load<false>(logits + (size_t)b * V, V, temperature, uniforms + b, active ? active + b : nullptr, z, u)) {
         if (tid == 0) out[b] = -1;
-        return;
-    }
-#pragma unroll
-    for (int j = 0; j < kSampPer; ++j) {
-        if (kSampThreads * j >= V) continue;  // uniform: slots past the row stay -inf
-        const float v = greedy ? z[j] : z[j] / temperature;
-        z[j] = v != v ? -INFINITY : v;
-    }
-    if (greedy) {
-        float bv;
-        int bi;
-        lane_best(z, 0, bv, bi);
-        block_best(bv, bi, rv, ri);
-        if (tid == 0) out[b] = bi < V ? bi : 0;
         return;
     }
     float lm = -INFINITY;
@@ -446,13 +464,15 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
     if (V <= kSampShort) {
         __syncthreads();
     } else {
-        if (top_k <= min(kSampWaves, V / kWave)) {
-            const float wm = wave_max(lm);
-            if (lane == 0) rv[wave] = wm;
+        int holders = kSampThreads;  // threads with an entry above -inf, where that is known
+        if constexpr (G < kSampThreads / 4) {
+            const float gm = group_max<kSampThreads / G>(lm);
+            if ((lane & (kSampThreads / G - 1)) == 0) s_gm[tid / (kSampThreads / G)] = gm;
             __syncthreads();
-            t = kth_largest<kSampWaves>(rv, lane & (kSampWaves - 1), top_k);
+            t = kth_largest<G>(s_gm, lane & (G - 1), top_k);
+            if (t == -INFINITY) holders = __syncthreads_count(lm > -INFINITY);
         }
-        if (t == -INFINITY) {  // (uniform over the workgroup)
+        if (t == -INFINITY && holders > kSampFew) {  // (uniform over the workgroup)
             const float gm = group_max<4>(lm);
             if ((lane & 3) == 0) s_gm[tid >> 2] = gm;
             __syncthreads();
@@ -550,8 +570,15 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
 hipError_t launch_sample(const float* logits, int B, int V, const ftts_sampling& s, const float* uniforms,
                          const int32_t* active, int32_t* out, hipStream_t st) {
     if (V > kSampThreads * kSampPer || s.top_k < 1 || s.top_k > FTTS_MAX_TOP_K) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(sample_kernel, dim3(B), dim3(kSampThreads), 0, st, logits, V, s.temperature, s.top_k,
-                       s.top_p, uniforms, active, out);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(B), dim3(kSampThreads), 0, st, logits, V, s.temperature, s.top_k, s.top_p, uniforms,
+                           active, out);
+    };
+    // as few groups as give a threshold near the k-th best, where the row reaches k of them
+    if (s.top_k == 1) hipLaunchKernelGGL(greedy_kernel, dim3(B), dim3(kSampThreads), 0, st, logits, V, active, out);
+    else if (s.top_k <= std::min(16, V / 64)) launch(sample_kernel<16>);
+    else if (s.top_k <= std::min(32, V / 16)) launch(sample_kernel<64>);
+    else launch(sample_kernel<256>);
     return hipGetLastError();
 }
 
