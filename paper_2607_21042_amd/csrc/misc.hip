@@ -95,8 +95,8 @@ __global__ __launch_bounds__(256) void ln_rows_kernel(const float* x, const void
 // lane): the row stays in registers, both reductions are cross-lane, no barriers.  Short
 // launches are bound by their dependent loads, so the gains and biases are requested
 // with the row (bf16; asked for after the reductions they cost another trip to memory).
-// Measured per launch, before (gains last, width a runtime value) and now: 256 x 1280
-// 4.7 and 4.5 us, 9,906 x 1280 15.7 and 14.0, 1000 x 768 4.1 and 4.0.
+// Traced in a call, before (gains last, width a runtime value) and now: 256 x 1280 5.0 and
+// 3.9 us, 10,827 x 1280 15.6 and 13.8, 1000 x 768 4.4 and 4.4, 11,154 x 768 11.0 and 9.0.
 template <bool F32, int N>
 __global__ __launch_bounds__(256) void ln_rows_wave_kernel(const float* x, const void* g, const void* bb, float eps,
                                                            int M, int d, void* out) {
@@ -300,18 +300,20 @@ hipError_t launch_assemble_prefix(int wdtype, const AssembleArgs& a, int rows, h
 // ranked by counting the keys above it, and ranks below k fill the ordered top-k list.
 // t = -inf, all entries above -inf, serves rows of up to kSampShort entries and rows masked
 // so that few threads hold one; if there are fewer than k, the lowest-index -inf
-// entries take the ranks after them.  Rows with more than kSampCand candidates (massive
-// exact ties, or many entries in few groups) take k rounds of block argmax instead.
+// entries take the ranks after them.  Where the candidates exceed kSampShort (a crowd of
+// equal entries, as in a row masked with a finite value), the best of the waves' own k-th
+// largest lane maxima is tried; rows that still have more than kSampCand take k rounds of
+// block argmax.
 //
 // A row is 33 KB, so the kernel is bound by its chain of short steps.  Measured, us a call:
 // 32 rows of 8194 at k = 30: 8.2 (10.2 with 256 groups for every k; 24 with 256 threads, a threshold per
 // wave that let about 180 candidates through, ranked one LDS read at a time); at k = 10
-// 8.9 (9.9 with 256 groups), k = 64 12.0; 100 entries 7.8 and 8194 masked to a run of 90 8.6 at
-// k = 30 (50 and 57 by rounds of argmax); 1024 rows of 16384, bound by reading them, 14.0
+// 8.9 (9.9 with 256 groups), k = 64 12.0; at k = 30 100 entries 7.8, 8194 masked to a run of 90
+// by -inf 8.6, by a finite value 11.4 (50-57 by rounds of argmax); 1024 rows of 16384, bound by reading them, 14.0
 // greedy and 17.0 at k = 2 (25.1 with 256 groups).
 constexpr int kSampThreads = 1024, kSampWaves = kSampThreads / kWave, kSampPer = 16;  // vocab <= 16384
 constexpr int kSampCand = 1024;
-constexpr int kSampFew = 128;     // as are all entries above -inf of a masked row if no more threads than this hold one
+constexpr int kSampFew = 128;    // masked rows: so few threads hold an entry above -inf that all of them are candidates
 constexpr int kSampShort = 256;  // rows of up to this many entries are ranked whole
 
 __device__ __forceinline__ bool beats(float v, int i, float bv, int bi) {
@@ -443,6 +445,7 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
                                                               int top_k, float top_p, const float* uniforms,
                                                               const int32_t* active, int32_t* out) {
     __shared__ __attribute__((aligned(16))) float s_gm[kSampThreads / 4];  // group maxima
+    __shared__ __attribute__((aligned(16))) float s_lane[kSampThreads];    // lane maxima
     __shared__ __attribute__((aligned(16))) uint64_t s_key[kSampCand + 8];
     __shared__ float selv[FTTS_MAX_TOP_K];
     __shared__ int seli[FTTS_MAX_TOP_K];
@@ -487,18 +490,38 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
         }
     }
     t = fmaxf(t, -FLT_MAX);  // (neither the slots past the row nor masked entries compete)
-    if (lm >= t) {
+    auto collect = [&] {
+        if (lm >= t) {
 #pragma unroll
-        for (int j = 0; j < kSampPer; ++j)
-            if (z[j] >= t) {
-                const int c = atomicAdd(&s_cnt, 1);
-                // larger value first, then lower index (+ 0.f: -0 ties with +0)
-                const uint32_t u = __float_as_uint(z[j] + 0.f), k = (u >> 31) ? ~u : u | 0x80000000u;
-                if (c < kSampCand) s_key[c] = ((uint64_t)k << 32) | (uint32_t)(0x7FFFFFFF - (tid + kSampThreads * j));
-            }
+            for (int j = 0; j < kSampPer; ++j)
+                if (z[j] >= t) {
+                    const int c = atomicAdd(&s_cnt, 1);
+                    // larger value first, then lower index (+ 0.f: -0 ties with +0)
+                    const uint32_t u = __float_as_uint(z[j] + 0.f), k = (u >> 31) ? ~u : u | 0x80000000u;
+                    if (c < kSampCand) s_key[c] = ((uint64_t)k << 32) | (uint32_t)(0x7FFFFFFF - (tid + kSampThreads * j));
+                }
+        }
+        __syncthreads();
+        return s_cnt;
+    };
+    int total = collect();
+    if (total > kSampShort) {
+        // A crowd of equal entries at t, as a mask with a finite value leaves: the k-th largest
+        // lane maximum of any one wave bounds the k best as well, and may lie above it.
+        s_lane[tid] = lm;
+        __syncthreads();
+        const float tw = kth_largest<kWave>(s_lane + wave * kWave, lane, top_k);
+        if (lane == 0) rv[wave] = tw;
+        __syncthreads();
+        float t2 = rv[0];
+        for (int w = 1; w < kSampWaves; ++w) t2 = fmaxf(t2, rv[w]);
+        if (t2 > t) {  // (uniform over the workgroup)
+            t = t2;
+            if (tid == 0) s_cnt = 0;
+            __syncthreads();
+            total = collect();
+        }
     }
-    __syncthreads();
-    const int total = s_cnt;
     if (total <= kSampCand) {
         if (tid < 8) s_key[total + tid] = 0;  // below every key, so that the ranking reads whole groups of 8
         if (total < top_k && wave == 0) {  // at least k - total of the first k <= 64 entries are -inf

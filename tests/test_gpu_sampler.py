@@ -101,18 +101,18 @@ def test_sampler_few_finite_entries(V):
             assert got[b] == want or osample.near_boundary(det), (T, k, p, b, got[b], want)
 
 
-def us_per_call(z, k, calls=100):
+def us_per_call(z, k, temperature=0.8, calls=100):
     import torch
     from paper_2607_21042_amd import ftts
     u = torch.from_numpy(workload.uniforms(1, z.shape[0], seed=9)[0]).cuda()
     out = torch.empty(z.shape[0], dtype=torch.int32, device="cuda")
-    ftts.sample(z, ftts.Sampling(0.8, k, 0.8), u, out)
+    ftts.sample(z, ftts.Sampling(temperature, k, 0.8), u, out)
     best = 1e9
     for _ in range(5):
         a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
         a.record()
         for _ in range(calls):
-            ftts.sample(z, ftts.Sampling(0.8, k, 0.8), u, out)
+            ftts.sample(z, ftts.Sampling(temperature, k, 0.8), u, out)
         b.record()
         torch.cuda.synchronize()
         best = min(best, a.elapsed_time(b) * 1000 / calls)
@@ -143,3 +143,50 @@ def test_small_top_k_over_many_rows_stays_near_the_read():
     t = {k: us_per_call(z, k) for k in (1, 2, 5)}
     print(f"sampler us per call of 1024 rows: {t}", flush=True)
     assert max(t[2], t[5]) <= 1.35 * t[1], t
+
+
+def test_rows_masked_with_a_finite_value_take_the_ranked_list():
+    """A run of 90 entries, the rest at float32's lowest value or at -1e4: the crowd of
+    equal entries may not send the row to k rounds of block argmax (57 us for 32 rows)."""
+    import torch
+    full = torch.from_numpy(workload.random_logits(32, 8194, seed=5)).cuda()
+    t = {"full": us_per_call(full, 30, temperature=1.0)}
+    for low in (float(np.finfo(np.float32).min), -1e4):
+        for V, at in ((8194, 4000), (1024, 500)):
+            z = torch.full((32, V), low, device="cuda")
+            z[:, at:at + 90] = full[:, at:at + 90]
+            t[low, V] = us_per_call(z, 30, temperature=1.0)
+    print(f"sampler us per call: {t}", flush=True)
+    assert max(t.values()) <= 2 * t["full"], t
+
+
+@pytest.mark.parametrize("low", [-np.inf, float(np.finfo(np.float32).min), -1e4])
+@pytest.mark.parametrize("k", [2, 9, 16, 30, 32, 64])
+def test_sampler_masked_rows_around_the_lines(k, low):
+    """V = 16384 with all but some entries masked, by -inf or a finite value: runs whose threads number 127 to 129
+    (the line for taking every entry above -inf), longer runs, and entries at the same
+    few threads' slots only (2048 of them: more than the candidate list holds)."""
+    import torch
+    from paper_2607_21042_amd import ftts
+    V = 16384
+    src = workload.random_logits(1, V, seed=k)[0]
+    rows = []
+    for n in (127, 128, 129, 300, 1000, 1025):
+        for at in (0, 1000, V - n):
+            z = np.full(V, low, np.float32)
+            z[at:at + n] = src[at:at + n]
+            rows.append(z)
+    for threads in (4, 64, 128, 129, 200):
+        z = np.full(V, low, np.float32)
+        keep = np.arange(V) % 1024 < threads
+        z[keep] = src[keep]
+        rows.append(z)
+    z = np.stack(rows)
+    u = workload.uniforms(1, len(rows), seed=k + 1)[0]
+    out = torch.empty(len(rows), dtype=torch.int32, device="cuda")
+    print(f"sampler, masked rows around the lines: k={k}", flush=True)
+    ftts.sample(torch.from_numpy(z).cuda(), ftts.Sampling(1.1, k, 0.95), torch.from_numpy(u).cuda(), out)
+    got = out.cpu().numpy()
+    for b in range(len(rows)):
+        want, det = osample.sample(z[b], 1.1, k, 0.95, u[b])
+        assert got[b] == want or osample.near_boundary(det), (k, b, got[b], want)
