@@ -90,7 +90,8 @@ def copy_calibration():
 
 
 MEGA_SOURCES = ("decode_mega.hip", "ftts_internal.hpp", "gemv_impl.hpp", "kv_page.hpp")
-BATCHED_SOURCES = ("bgemm.hip", "attention.hip", "misc.hip", "ftts.hip", "ftts_internal.hpp", "kv_page.hpp")
+BATCHED_SOURCES = ("bgemm.hip", "bgemm_stage.hpp", "gemm_epilogue.hpp", "attention.hip", "misc.hip", "ftts.hip",
+                   "ftts_internal.hpp", "kv_page.hpp")
 
 
 def kernel_sources_sha(files=MEGA_SOURCES) -> str:

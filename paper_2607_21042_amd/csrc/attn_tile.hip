@@ -16,9 +16,9 @@
 // (probabilities then stay below 256; nothing is lost in fp32), and masks are applied
 // in a tile that needs one only.
 //
-// Measured (us per layer): 32 causal prefixes, 9,906 rows, 20 heads, 93 -> 43 (before: K
+// Traced (us per layer): 32 causal prefixes, 10,827 rows, 20 heads, 86 -> 41 (before: K
 // rows read per wave from L2 with nothing in flight, V transposed through registers); 24
-// sequences of 170-730 frames, 12 heads, 58 -> 43 (32-key tiles staged through
+// sequences of 170-730 frames, 12 heads, 56 -> 42 (32-key tiles staged through
 // registers).  Three stages measured 44 / 45, four workgroups a CU spill (causal: 101).
 //
 // Pieces of 16 bytes are XOR-swizzled by (row / 2) % 8 (two rows share the 256 bytes that
@@ -319,9 +319,9 @@ __global__ __launch_bounds__(kAtWaves * 64, 3) void attn_tile_kernel(const AttnP
 // a tile's K (V) operands are in registers the next tile's K (V) loads go out to the same
 // place and land during the products; no barrier in the loop.  The four (max, sum, output) partials are merged by
 // the log-sum-exp rule through LDS at the end.  Two workgroups a CU.  Bound by
-// the chain load, product, softmax, product, merge.  Measured (us per layer), before
+// the chain load, product, softmax, product, merge.  Traced (us per layer), before
 // (32-key tiles, V transposed through registers) and now: 2 x 500 frames, 12 heads, no
-// mask, 12.7 and 10.5; 256 causal rows, 20 heads, 6.2 and 6.1.
+// mask, 12.5 and 10.4; 256 causal rows, 20 heads, 6.5 and 6.4.
 //
 // LAST: one workgroup per (sequence, head) that keeps only the last query, as row s of the
 // output: all that the layer feeding the logits needs.

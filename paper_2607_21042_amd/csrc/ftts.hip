@@ -736,8 +736,8 @@ static int prefill(const ftts_weights* w, const PrefixSource& src, const int32_t
     const GemmPlan p_fc1 = gemm_plan(c.wdtype, Mi, F, d), p_fc2 = gemm_plan(c.wdtype, Mi, d, F);
     // The last layer's rows beyond each prefix's last one feed nothing but its own K and V
     // (16-bit): after its QKV product it goes on with the B last rows, or ends there without
-    // logits.  The launches after QKV, all rows and last rows: 394 and 65 us for 32 prefixes
-    // of 9,906 rows in all, 51 and 36 us for one of 256 rows.
+    // logits.  The kernels after QKV, all rows and last rows, traced: 380 and 54 us for 32
+    // prefixes of 10,827 rows in all, 50 and 38 us for one of 256 rows.
     const bool trim = c.wdtype != FTTS_F32;
     float* x = P.x;
     for (int l = 0; l < c.n_layer; ++l) {

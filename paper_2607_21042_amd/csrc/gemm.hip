@@ -96,8 +96,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const GemmArgs a) {
 // on 256 CUs, about 650 timings of 24 (N, K) x M shapes (66 to 10,800 rows, N and K
 // 768-5120) over every tile shape and K split, with enough weight copies in turn that
 // they come from where a model's weights do (500 MB for the GPT's widths, 190 MB for
-// the DiT's); rms error 4-10%.  Choosing by the model costs 0.5% on average over the
-// best timed choice of a shape (14% at worst).  No rule on one dimension does: 1000 x
+// the DiT's); rms error 4-10% of those timings, which are of bare products: the model has
+// no term for what an epilogue reads, computes and writes, which the launches compared for a
+// shape share.  In the calls themselves launches take 13% longer than modelled on
+// average (-7 to +39%): 256 x 5120 x 1280 + GELU 11.0 modelled and 15.1 traced, 10,827 x
+// 1280 x 1280 residual 37.1 and 51.6, 10,827 x 3840 x 1280 99.4 and 107.8, 697 x 1280 x
+// 5120 int8 22.6 and 24.9, 1000 x 3072 x 768 + GELU 11.8 and 12.9.  Choosing by the model costs 0.5%
+// on average over the best timed choice of a shape (14% at worst).  No rule on one dimension does: 1000 x
 // 5120 x 1280 takes 20.6 us in 128 x 256 tiles against 25.5 / 28.3 in 64 x 128 / 64 x
 // 64, 1000 x 1280 x 1280 20.0 against 12.1 / 11.4, 10,800 x 5120 x 1280 138 in 256 x
 // 256, 7,000 x 5120 x 1280 88 in 192 x 256 against 100.

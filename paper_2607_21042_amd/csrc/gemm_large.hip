@@ -24,9 +24,10 @@
 //    shape, and rows past the last full round can go to the small kernel
 //    (gemm_plan).  9,746 x 5120 x 1280 is 780 tiles of 256 x 256 -- four rounds on
 //    256 CUs, the last with 12 tiles -- but four full rounds of 192 rows.
-// Measured (us per GEMM, before -> now; a pass of 32 prefixes, 9,746 rows): QKV
-// 133 -> 89 (1080 TFLOP/s), FC1 + GELU 175 -> 126, out-projection 52 -> 41, FC2
-// 155 -> 108.
+// Traced in the calls (us per GEMM, before -> now): 32 prefixes of 10,827 rows, QKV 129
+// -> 108 (987 TFLOP/s), FC1 + GELU 171 -> 143 (its last rows on the small kernel), out-projection 53 -> 52,
+// FC2 148 -> 126 (1,124 TFLOP/s); 11,154 rows of width 768, QKV 55 -> 43, FC1 + GELU 90 -> 67,
+// out-projection 34 -> 27, FC2 91 -> 61.
 //
 // K loop: the 8 waves form two groups of 4 (one wave of each per SIMD) half a
 // phase apart: while one group runs its matrix instructions the other reads its

@@ -13,10 +13,10 @@
 // 128-column group (a stage) for W4A16.
 //
 // Against the kernel it replaces (register staging, one 64-column step ahead, K
-// split up to 8 ways to fill the chip; us per GEMM in a graph): 256 x 3840 x 1280
-// 16.5 -> 8.3, 256 x 1280 x 1280 12.6 -> 8.1, 256 x 5120 x 1280 + GELU 20.4 -> 14.6,
-// 256 x 1280 x 5120 23.6 -> 14.8, 1000 x 768 x 768 9.7 -> 6.4, 1000 x 3072 x 768 +
-// GELU 14.2 -> 11.5.
+// split up to 8 ways to fill the chip; us per GEMM traced in the calls): 256 x 3840 x
+// 1280 16.4 -> 10.6, 256 x 1280 x 1280 13.2 -> 8.7, 256 x 5120 x 1280 + GELU 20.2 ->
+// 15.1, 256 x 1280 x 5120 23.2 -> 15.9, 1000 x 768 x 768 11.0 -> 6.7, 1000 x 768 x 3072
+// 17.3 -> 16.1; int8 weights, 697 rows: 23.9 -> 19.0, 16.0 -> 9.5, 24.7 -> 19.4, 33.9 -> 24.9.
 //
 // Splitting K pays only where whole tiles would leave most of the chip idle over a
 // long K (the plan's model decides): every slice stores its fp32 partial tile and the last of a
