@@ -554,6 +554,7 @@ __global__ __launch_bounds__(kSampThreads) void sample_kernel(const float* logit
         uint32_t taken = 0;
         float bv;
         int bi;
+        __syncthreads();  // every thread has read the waves' thresholds in rv
         lane_best(z, taken, bv, bi);
         for (int r = 0; r < top_k; ++r) {
             float wv = bv;
